@@ -165,22 +165,21 @@ def _untie(x, Wg, bias, k):
     x.copy_(torch.where(tied[:, None], x[torch.argmin(tied.to(torch.int32))], x))
 
 
-def prepare(case, seed):
-    c, dev = dict(case), "cuda"
+def _inputs(c, seed):
+    """The raw inputs of a case, made from the seed alone: the rows of "ffn", or router matrix, bias and activations,
+    and the expert weights W1, W3, W2 (none for "route")."""
+    dev = "cuda"
     g = torch.Generator(device=dev).manual_seed(1000003 * seed + 17)
     T, d, f, E, k, El = c["T"], c["d"], c["f"], c["E"], c["k"], c["E_local"]
 
     def normal(*shape, dtype=torch.bfloat16, std=1.0):
         return torch.empty(shape, dtype=dtype, device=dev).normal_(0.0, std, generator=g)
 
-    s = dict(mode=c["mode"], T=T)
+    r = {}
     if c["mode"] == "ffn":
         # rows arrive expert-contiguous; the host knows how many it received
-        ctx = moe.MoEContext(max(1, -(-T // k)), d, f, E, k, c["e_lo"], El)
-        s["xp"], s["offsets"] = normal(T, d), _zipf_offsets(T, El, seed).to(dev)
+        r["xp"], r["offsets"] = normal(T, d), _zipf_offsets(T, El, seed).to(dev)
     else:
-        t_max = T if c["shape"] in ("tiny", "free", "trace") else max(T, T_SERVE)
-        ctx = moe.MoEContext(t_max, d, f, E, k, c["e_lo"], El)
         Wg = normal(d, E, dtype=torch.float32, std=c["wg"])
         bias = _bias(c, seed)
         xs = [normal(T, d) for _ in range(c["steps"])]
@@ -193,14 +192,30 @@ def prepare(case, seed):
                     x[t0:t1] = (x[t0:t1].float() + 20.0 * u).to(torch.bfloat16)
                 for e in pair:
                     Wg[:, e] += 0.5 * u
-        s["bias"] = None if bias is None else bias.to(dev)
+        r["bias"] = None if bias is None else bias.to(dev)
         for x in xs:
-            _untie(x, Wg, s["bias"], k)
-        s["xs"], s["router"] = xs, ctx.moe_pack_router(Wg)
-        s["counts"] = torch.zeros(c["steps"], E, dtype=torch.int32, device=dev)
+            _untie(x, Wg, r["bias"], k)
+        r["xs"], r["Wg"] = xs, Wg
     if c["mode"] != "route":
-        s["packed"] = ctx.moe_pack_weights(normal(El, d, f, std=W_STD), normal(El, d, f, std=W_STD),
-                                           normal(El, f, d, std=W_STD))
+        r["experts"] = [normal(El, d, f, std=W_STD), normal(El, d, f, std=W_STD), normal(El, f, d, std=W_STD)]
+    return r
+
+
+def prepare(case, seed):
+    c = dict(case)
+    T, d, f, E, k, El = c["T"], c["d"], c["f"], c["E"], c["k"], c["E_local"]
+    r = _inputs(c, seed)
+    s = dict(mode=c["mode"], T=T)
+    if c["mode"] == "ffn":
+        ctx = moe.MoEContext(max(1, -(-T // k)), d, f, E, k, c["e_lo"], El)
+        s["xp"], s["offsets"] = r["xp"], r["offsets"]
+    else:
+        t_max = T if c["shape"] in ("tiny", "free", "trace") else max(T, T_SERVE)
+        ctx = moe.MoEContext(t_max, d, f, E, k, c["e_lo"], El)
+        s["bias"], s["xs"], s["router"] = r["bias"], r["xs"], ctx.moe_pack_router(r["Wg"])
+        s["counts"] = torch.zeros(c["steps"], E, dtype=torch.int32, device="cuda")
+    if c["mode"] != "route":
+        s["packed"] = ctx.moe_pack_weights(*r["experts"])
     s["ctx"] = ctx
     return s
 
@@ -219,6 +234,42 @@ def run(s):
     xp, offsets, row_of, _ = ctx.moe_permute(x, idx)
     y = ctx.moe_grouped_ffn(xp, offsets, ctx.rows_capacity(s["T"]), s["packed"])
     return ctx.moe_combine(y, row_of, w)
+
+
+# ---- the same results in 64 bits ---------------------------------------------------------------------------
+def _ffn64(r, rows, e):
+    """Rows of one expert through its SwiGLU network, in 64 bits."""
+    W1, W3, W2 = (w[e].double() for w in r["experts"])
+    g = rows @ W1
+    return (g * torch.sigmoid(g) * (rows @ W3)) @ W2
+
+
+def exact(case, seed):
+    c = dict(case)
+    r = _inputs(c, seed)
+    if c["mode"] == "ffn":
+        off, y = r["offsets"].tolist(), torch.zeros(c["T"], c["d"], dtype=torch.float64, device="cuda")
+        for e in range(c["E_local"]):
+            if off[e + 1] > off[e]:
+                y[off[e]:off[e + 1]] = _ffn64(r, r["xp"][off[e]:off[e + 1]].double(), e)
+        return y
+    routed = []
+    for x in r["xs"]:
+        logits = x.double() @ r["Wg"].double()
+        if r["bias"] is not None:
+            logits += r["bias"].double()
+        top = logits.topk(c["k"], dim=1)
+        routed.append((top.indices, torch.softmax(top.values, dim=1)))
+    if c["mode"] == "route":
+        counts = torch.stack([torch.bincount(i.reshape(-1), minlength=c["E"]) for i, _ in routed])
+        return [t for i, w in routed for t in (i.to(torch.int32), w)] + [counts.to(torch.int32)]
+    x, (idx, w) = r["xs"][0], routed[0]
+    out = torch.zeros(c["T"], c["d"], dtype=torch.float64, device="cuda")
+    for e in range(c["E_local"]):
+        tok, slot = (idx == c["e_lo"] + e).nonzero(as_tuple=True)
+        if tok.numel():
+            out.index_add_(0, tok, w[tok, slot, None] * _ffn64(r, x[tok].double(), e))
+    return out
 
 
 # ---- what a pass cannot do without, and how closely two correct passes agree --------------------------------
