@@ -88,6 +88,13 @@ hipError_t gemm_init_attributes() {
     return err;
 }
 
+// Workgroups that build a list of `grid` entries: one entry per thread (an entry is a few thousand cycles of
+// dependent integer work)
+static int sched_list_blocks(int grid) {
+    const int blocks = (grid + 255) / 256;
+    return blocks < 1 ? 1 : blocks > 64 ? 64 : blocks;
+}
+
 SchedArgs gemm_sched_args(const GemmPlan& p, int E_local, TileDesc* t1, TileDesc* t2, int nsplit2, int64_t rows_cap,
                           int32_t* refused) {
     SchedArgs a;
@@ -97,17 +104,12 @@ SchedArgs gemm_sched_args(const GemmPlan& p, int E_local, TileDesc* t1, TileDesc
     a.nt2 = p.nt2; a.grid2 = p.grid2; a.t2 = t2;
     a.nsplit1 = 1; a.nsplit2 = nsplit2;
     a.rows_cap = (int)rows_cap;
+    a.parts1 = sched_list_blocks(p.grid1);
     a.refused_out = refused;
     return a;
 }
 
-int gemm_sched_blocks(const GemmPlan& p) {
-    int g = p.grid1 > p.grid2 ? p.grid1 : p.grid2;
-    int blocks = (g + 255) / 256;  // one entry per thread: an entry is a few thousand cycles of dependent integer work
-    if (blocks < 1) blocks = 1;
-    if (blocks > 64) blocks = 64;
-    return blocks;
-}
+int gemm_sched_blocks(const GemmPlan& p) { return sched_list_blocks(p.grid1) + sched_list_blocks(p.grid2); }
 
 hipError_t launch_schedule(const GemmPlan& p, const int32_t* offsets, int E_local, TileDesc* t1, TileDesc* t2,
                            int nsplit2, int64_t rows_cap, int32_t* refused, hipStream_t st) {
@@ -267,8 +269,9 @@ hipError_t launch_router_gemm(const uint16_t* x, const uint16_t* rp, int T, int 
         a.nt2 = 0; a.grid2 = 0; a.t2 = nullptr;
         a.nsplit1 = pk.nsplit; a.nsplit2 = 1;
         a.rows_cap = -1;
+        a.parts1 = (grid + 1023) / 1024;
         a.refused_out = nullptr;
-        hipLaunchKernelGGL(schedule_kernel, dim3((grid + 1023) / 1024), dim3(256), 0, st, (const int32_t*)nullptr, T, a);
+        hipLaunchKernelGGL(schedule_kernel, dim3(a.parts1), dim3(256), 0, st, (const int32_t*)nullptr, T, a);
         hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;
         if (*table_T != -2) *table_T = T;

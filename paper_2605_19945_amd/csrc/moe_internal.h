@@ -42,6 +42,7 @@ struct SchedArgs {
     TileDesc* t2;
     int nsplit1, nsplit2;  // reduction splits (workgroups per entry) of the two launches
     int rows_cap;          // host bound on the total rows (-1: none); exceeded -> nothing is scheduled
+    int parts1;            // workgroups that build the first list (all others: the second)
     int32_t* refused_out;  // where that refusal is recorded (or nullptr)
 };
 
