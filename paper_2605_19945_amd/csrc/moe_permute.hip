@@ -512,6 +512,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ 
 // The same sum when the second GEMM ran as nsplit reduction ranges: the expert output row is first formed from
 // its partial sums (added in slab order, rounded to bf16 exactly as reduce_splits_kernel stores it), so the
 // result equals moe_combine on the reduced rows bit for bit and the reduced rows are never written.
+constexpr int MAX_SPLIT2 = 8;  // reduction ranges of the second GEMM, at most (gemm_pick_split2)
 __global__ __launch_bounds__(256) void combine_split_kernel(const float* __restrict__ part, int nsplit,
                                                             size_t slab_elems, const int32_t* __restrict__ row_of,
                                                             const float* __restrict__ w, int T, int k, int chunks,
@@ -527,12 +528,22 @@ __global__ __launch_bounds__(256) void combine_split_kernel(const float* __restr
         if (r < 0) continue;
         const float g = w[(size_t)t * k + j];
         const float* src = part + ((size_t)r * chunks + c) * 8;
-        f32x4_t lo = *(const f32x4_t*)src, hi = *(const f32x4_t*)(src + 4);
-        for (int sp = 1; sp < nsplit; ++sp) {
-            const f32x4_t l2 = *(const f32x4_t*)(src + sp * slab_elems), h2 = *(const f32x4_t*)(src + sp * slab_elems + 4);
-            lo[0] += l2[0]; lo[1] += l2[1]; lo[2] += l2[2]; lo[3] += l2[3];
-            hi[0] += h2[0]; hi[1] += h2[1]; hi[2] += h2[2]; hi[3] += h2[3];
-        }
+        // all slabs are requested before the first is used (one after the other they are nsplit round
+        // trips: Mixtral shape, 1 token, 7 slabs 5.9 -> 4.5 us)
+        f32x4_t l[MAX_SPLIT2], h[MAX_SPLIT2];
+#pragma unroll
+        for (int sp = 0; sp < MAX_SPLIT2; ++sp)
+            if (sp < nsplit) {  // uniform
+                l[sp] = *(const f32x4_t*)(src + sp * slab_elems);
+                h[sp] = *(const f32x4_t*)(src + sp * slab_elems + 4);
+            }
+        f32x4_t lo = l[0], hi = h[0];
+#pragma unroll
+        for (int sp = 1; sp < MAX_SPLIT2; ++sp)
+            if (sp < nsplit) {
+                lo[0] += l[sp][0]; lo[1] += l[sp][1]; lo[2] += l[sp][2]; lo[3] += l[sp][3];
+                hi[0] += h[sp][0]; hi[1] += h[sp][1]; hi[2] += h[sp][2]; hi[3] += h[sp][3];
+            }
         for (int q = 0; q < 4; ++q) {
             acc[q] += g * (float)(__bf16)lo[q];
             acc[4 + q] += g * (float)(__bf16)hi[q];
