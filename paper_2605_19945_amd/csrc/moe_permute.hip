@@ -509,12 +509,20 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ 
     else out[(size_t)t * chunks + c] = o;
 }
 
-// The same sum when the second GEMM ran as nsplit reduction ranges: the expert output row is first formed from
+// The same sum when the second GEMM ran as NS reduction ranges: the expert output row is first formed from
 // its partial sums (added in slab order, rounded to bf16 exactly as reduce_splits_kernel stores it), so the
 // result equals moe_combine on the reduced rows bit for bit and the reduced rows are never written.
+//
+// All slabs of a row are requested before the first is used: one after the other they are NS round trips, and with
+// one token there is nothing else to wait for (Mixtral shape, 1 token, 8 slabs: 6.2 us serial, 4.6 together).  NS is
+// a template parameter so that a lane holds 8 * NS registers of partial sums and no more: from a few hundred tokens
+// on the kernel is bound by the bytes its wavefronts keep in flight, and one kernel with room for eight slabs (82
+// registers, 5 wavefronts per SIMD instead of 8) loses there (us, serial / room for eight / this: Mixtral shape, 2
+// slabs, 512 tokens 7.3 / 7.8 / 7.3, 768 tokens 9.9 / 10.8 / 9.9; 16 wide experts, 1000 tokens 9.0 / 9.9 / 8.8).
 constexpr int MAX_SPLIT2 = 8;  // reduction ranges of the second GEMM, at most (gemm_pick_split2)
-__global__ __launch_bounds__(256) void combine_split_kernel(const float* __restrict__ part, int nsplit,
-                                                            size_t slab_elems, const int32_t* __restrict__ row_of,
+template <int NS>
+__global__ __launch_bounds__(256) void combine_split_kernel(const float* __restrict__ part, size_t slab_elems,
+                                                            const int32_t* __restrict__ row_of,
                                                             const float* __restrict__ w, int T, int k, int chunks,
                                                             uint4* __restrict__ out) {
     const int chunks_per_block = blockDim.x;
@@ -528,22 +536,19 @@ __global__ __launch_bounds__(256) void combine_split_kernel(const float* __restr
         if (r < 0) continue;
         const float g = w[(size_t)t * k + j];
         const float* src = part + ((size_t)r * chunks + c) * 8;
-        // all slabs are requested before the first is used (one after the other they are nsplit round
-        // trips: Mixtral shape, 1 token, 7 slabs 5.9 -> 4.5 us)
-        f32x4_t l[MAX_SPLIT2], h[MAX_SPLIT2];
+        f32x4_t l[NS], h[NS];
 #pragma unroll
-        for (int sp = 0; sp < MAX_SPLIT2; ++sp)
-            if (sp < nsplit) {  // uniform
-                l[sp] = *(const f32x4_t*)(src + sp * slab_elems);
-                h[sp] = *(const f32x4_t*)(src + sp * slab_elems + 4);
-            }
+        for (int sp = 0; sp < NS; ++sp) {
+            l[sp] = *(const f32x4_t*)(src + sp * slab_elems);
+            h[sp] = *(const f32x4_t*)(src + sp * slab_elems + 4);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // no addition moves up between the loads (the compiler would, to save registers)
         f32x4_t lo = l[0], hi = h[0];
 #pragma unroll
-        for (int sp = 1; sp < MAX_SPLIT2; ++sp)
-            if (sp < nsplit) {
-                lo[0] += l[sp][0]; lo[1] += l[sp][1]; lo[2] += l[sp][2]; lo[3] += l[sp][3];
-                hi[0] += h[sp][0]; hi[1] += h[sp][1]; hi[2] += h[sp][2]; hi[3] += h[sp][3];
-            }
+        for (int sp = 1; sp < NS; ++sp) {
+            lo[0] += l[sp][0]; lo[1] += l[sp][1]; lo[2] += l[sp][2]; lo[3] += l[sp][3];
+            hi[0] += h[sp][0]; hi[1] += h[sp][1]; hi[2] += h[sp][2]; hi[3] += h[sp][3];
+        }
         for (int q = 0; q < 4; ++q) {
             acc[q] += g * (float)(__bf16)lo[q];
             acc[4 + q] += g * (float)(__bf16)hi[q];
@@ -562,8 +567,20 @@ hipError_t launch_combine_split(const float* part, int nsplit, size_t slab_elems
     int chunks = d / 8;
     int threads = chunks >= 256 ? 256 : (chunks + 63) / 64 * 64;
     int blocks_per_row = (chunks + threads - 1) / threads;
-    hipLaunchKernelGGL(combine_split_kernel, dim3(T * blocks_per_row), dim3(threads), 0, st, part, nsplit, slab_elems,
-                       row_of, w, T, k, chunks, (uint4*)out);
+    static_assert(MAX_SPLIT2 == 8, "one instantiation per number of slabs");
+    decltype(&combine_split_kernel<2>) kernel;
+    switch (nsplit) {
+        case 2: kernel = combine_split_kernel<2>; break;
+        case 3: kernel = combine_split_kernel<3>; break;
+        case 4: kernel = combine_split_kernel<4>; break;
+        case 5: kernel = combine_split_kernel<5>; break;
+        case 6: kernel = combine_split_kernel<6>; break;
+        case 7: kernel = combine_split_kernel<7>; break;
+        case 8: kernel = combine_split_kernel<8>; break;
+        default: return hipErrorInvalidValue;
+    }
+    hipLaunchKernelGGL(kernel, dim3(T * blocks_per_row), dim3(threads), 0, st, part, slab_elems, row_of, w, T, k, chunks,
+                       (uint4*)out);
     return hipGetLastError();
 }
 
