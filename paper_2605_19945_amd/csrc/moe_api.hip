@@ -306,7 +306,7 @@ moe_status moe_pack_weights(moe_ctx* c, const void* W1, const void* W3, const vo
 // partial-logit slabs of T tokens that fit the workspace sized for T_max
 static int logits_slabs(const moe_ctx* c, int T) {
     int64_t n = (int64_t)moe_router_split_cap(c->s.T_max) * c->s.T_max / (T > 0 ? T : 1);
-    return n > 8 ? 8 : (int)n;
+    return n > MOE_MAX_SLABS ? MOE_MAX_SLABS : (int)n;
 }
 
 moe_status moe_route(moe_ctx* c, const void* x, const void* rp, const float* bias, int32_t T,

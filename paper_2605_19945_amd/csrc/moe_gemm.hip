@@ -150,7 +150,7 @@ int gemm_pick_split2(const GemmPlan& p, int64_t n_rows, int E_local, int d, int 
         // 149; 4 splits, one item per resident workgroup, 156; 8 splits 164)
         const double want = (double)SCHED_CU;
         int pick = 1;
-        for (int s = 1; s <= 8; ++s) {
+        for (int s = 1; s <= MOE_MAX_SLABS; ++s) {
             if (KT % s != 0 || KT / s < 16) continue;
             if ((double)s * n_rows * d * 4 > (double)part_bytes) continue;
             pick = s;
@@ -166,7 +166,7 @@ int gemm_pick_split2(const GemmPlan& p, int64_t n_rows, int E_local, int d, int 
     };
     int best = 1;
     double best_cost = cost(1) * 0.9;  // a split has to win by 10 %
-    for (int s = 2; s <= 8; ++s) {
+    for (int s = 2; s <= MOE_MAX_SLABS; ++s) {
         if (KT % s != 0 || KT / s < 16) continue;
         if ((double)s * n_rows * d * 4 > (double)part_bytes) continue;
         const double c = cost(s);
@@ -218,7 +218,7 @@ hipError_t launch_gemm2(const GemmPlan& p, const uint16_t* H, const uint16_t* W2
 // ---- router logits as a one-group GEMM (E >= 32): logits[T, Ep] = x[T, d] * Wg, fp32 ------------
 // Router rows are packed like W1|W3: 32-row blocks alternate between the high and the low bf16 term
 // of the same 32 experts, and the epilogue adds the two accumulators.  The output is tiny next to the
-// reduction length, so the reduction is split over up to 8 workgroups per tile (partial logits in
+// reduction length, so the reduction is split over up to MOE_MAX_SLABS workgroups per tile (partial logits in
 // consecutive [T, ldl] slabs, added in order by the top-k kernel) until every compute unit has work.
 struct RouterPick { int cls, nsplit; };
 static RouterPick router_gemm_pick(int T, int d, int Rp, int max_split) {
@@ -227,12 +227,12 @@ static RouterPick router_gemm_pick(int T, int d, int Rp, int max_split) {
     for (int i = 0; i < 4; ++i) {
         const int c = order[i];
         const int mt = (T + kClassRows[c] - 1) / kClassRows[c];
-        for (int s = 1; s <= 8 && s <= max_split; ++s)
+        for (int s = 1; s <= MOE_MAX_SLABS && s <= max_split; ++s)
             if (KT % s == 0 && KT / s >= 8 && mt * nt * s >= SCHED_CU) return {c, s};
     }
     // not enough work for the whole device whatever the shape: the 128-row tile, deepest allowed split
     int s = 1;
-    for (int t = 2; t <= 8 && t <= max_split; ++t)
+    for (int t = 2; t <= MOE_MAX_SLABS && t <= max_split; ++t)
         if (KT % t == 0 && KT / t >= 8) s = t;
     return {0, s};
 }

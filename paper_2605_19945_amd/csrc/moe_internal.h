@@ -93,9 +93,12 @@ struct moe_ctx {
 };
 
 static inline int64_t moe_round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
+// Ranges a reduction is split into, at most (second expert GEMM, router GEMM): what the pickers choose from, the
+// workspace holds and the kernels that add the slabs of partial sums are built for.
+constexpr int MOE_MAX_SLABS = 8;
 // Workspace for the partial sums of a split second GEMM: splits are only worth it at low loads
 static inline size_t moe_part_bytes(int64_t rows_cap, int d) {
-    const size_t want = (size_t)8 * rows_cap * d * 4, cap = (size_t)64 << 20;
+    const size_t want = (size_t)MOE_MAX_SLABS * rows_cap * d * 4, cap = (size_t)64 << 20;
     return want < cap ? want : cap;
 }
 // Leading dimension (elements) of the intermediate H, which the library lays out itself: rows are
@@ -146,7 +149,7 @@ int router_gemm_grid_max(int T_max, int Rp);
 hipError_t launch_router_gemm(const uint16_t* x, const uint16_t* rp, int T, int d, int Rp, float* logits, int ldl,
                               int max_split, int* nsplit_out, TileDesc* table, int* table_T, hipStream_t st);
 // Slabs of partial router logits ([T, cols] fp32 each) the workspace holds for T tokens
-static inline int moe_router_split_cap(int T) { return T <= 8192 ? 8 : T <= 16384 ? 4 : T <= 32768 ? 2 : 1; }
+static inline int moe_router_split_cap(int T) { return T <= 8192 ? MOE_MAX_SLABS : T <= 16384 ? 4 : T <= 32768 ? 2 : 1; }
 hipError_t launch_schedule(const GemmPlan& p, const int32_t* offsets, int E_local, TileDesc* t1,
                            TileDesc* t2, int nsplit2, int64_t rows_cap, int32_t* refused, hipStream_t st);
 // Arguments of a work-list build for plan p, and the workgroups worth spending on it

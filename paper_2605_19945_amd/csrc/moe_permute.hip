@@ -519,7 +519,6 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ 
 // on the kernel is bound by the bytes its wavefronts keep in flight, and one kernel with room for eight slabs (82
 // registers, 5 wavefronts per SIMD instead of 8) loses there (us, serial / room for eight / this: Mixtral shape, 2
 // slabs, 512 tokens 7.3 / 7.8 / 7.3, 768 tokens 9.9 / 10.8 / 9.9; 16 wide experts, 1000 tokens 9.0 / 9.9 / 8.8).
-constexpr int MAX_SPLIT2 = 8;  // reduction ranges of the second GEMM, at most (gemm_pick_split2)
 template <int NS>
 __global__ __launch_bounds__(256) void combine_split_kernel(const float* __restrict__ part, size_t slab_elems,
                                                             const int32_t* __restrict__ row_of,
@@ -567,7 +566,7 @@ hipError_t launch_combine_split(const float* part, int nsplit, size_t slab_elems
     int chunks = d / 8;
     int threads = chunks >= 256 ? 256 : (chunks + 63) / 64 * 64;
     int blocks_per_row = (chunks + threads - 1) / threads;
-    static_assert(MAX_SPLIT2 == 8, "one instantiation per number of slabs");
+    static_assert(MOE_MAX_SLABS == 8, "one instantiation per number of slabs");
     decltype(&combine_split_kernel<2>) kernel;
     switch (nsplit) {
         case 2: kernel = combine_split_kernel<2>; break;

@@ -374,7 +374,6 @@ __global__ __launch_bounds__(RR_NW * 64) void route_resident_kernel(
 // (picked by workgroup) so that the atomics on one address stay few; reduce_counts_kernel folds them
 // into counts[] and leaves them zero for the next call.
 constexpr int TOPK_SUB = 32;
-constexpr int ROUTER_MAX_SPLIT = 8;  // slabs of partial logits, at most (launch_router_gemm)
 template <int EPL>
 __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ logits, int ldl, int nsplit,
                                                    const float* __restrict__ bias, int T, int E, int k,
@@ -387,11 +386,11 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ log
     // The partial logits of the split reduction, added in slab order.  What bounds this kernel is latency: all the
     // slabs' values and the bias are requested before the first is added (one after the other they are nsplit memory
     // round trips: 256 experts, 2048 tokens, 8 slabs 12.1 -> 6.8 us; 128 experts, 8192 tokens, 4 slabs 10.4 -> 8.1).
-    float part[ROUTER_MAX_SPLIT][EPL], b[EPL];
+    float part[MOE_MAX_SLABS][EPL], b[EPL];
 #pragma unroll
     for (int j = 0; j < EPL; ++j) b[j] = bias != nullptr ? bias[min(lane + 64 * j, E - 1)] : 0.f;
 #pragma unroll
-    for (int sp = 0; sp < ROUTER_MAX_SPLIT; ++sp)
+    for (int sp = 0; sp < MOE_MAX_SLABS; ++sp)
         if (sp < nsplit) {  // uniform
 #pragma unroll
             for (int j = 0; j < EPL; ++j) part[sp][j] = logits[((size_t)sp * T + t) * ldl + min(lane + 64 * j, E - 1)];
@@ -400,7 +399,7 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ log
     for (int j = 0; j < EPL; ++j) {
         float v = part[0][j];
 #pragma unroll
-        for (int sp = 1; sp < ROUTER_MAX_SPLIT; ++sp)
+        for (int sp = 1; sp < MOE_MAX_SLABS; ++sp)
             if (sp < nsplit) v += part[sp][j];
         if (bias != nullptr) v += b[j];
         key[j] = lane + 64 * j < E ? float_order_bits(v) : 0u;
@@ -461,6 +460,7 @@ hipError_t launch_route(const uint16_t* x, const uint16_t* rp, const float* bias
         int nsplit = 1;
         err = launch_router_gemm(x, rp, T, d, 2 * Ep, logits_ws, Ep, logits_slabs, &nsplit, table_ws, table_T, st);
         if (err != hipSuccess) return err;
+        if (nsplit > MOE_MAX_SLABS) return hipErrorInvalidValue;  // the top-k kernel adds no more slabs than that
         const int blocks = (T + 3) / 4;
         const int epl = (E + 63) / 64;
         int32_t* sub = counts != nullptr ? route_ws + MOE_ROUTE_WS_SUBCOUNTS : nullptr;

@@ -103,6 +103,17 @@ def test_no_device_means_device_error_not_a_fallback(lib):
     assert not ctx.value
 
 
+def test_combine_refuses_a_number_of_slabs_it_has_no_kernel_for(lib):
+    """The launcher behind moe_layer_forward's combine: a number of partial-sum slabs outside 2..8 is an error
+    (hipErrorInvalidValue) before any launch, never a sum over fewer slabs."""
+    combine = lib._Z20launch_combine_splitPKfimPKiS0_iiiPtP12ihipStream_t
+    combine.restype = C.c_int
+    combine.argtypes = [C.c_void_p, C.c_int, C.c_size_t, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_void_p,
+                        C.c_void_p]
+    for slabs in (-1, 0, 1, 9, 16):
+        assert combine(None, slabs, 64, None, None, 1, 1, 64, None, None) == 1
+
+
 def test_product_package_does_not_touch_the_oracle():
     pkg = os.path.join(ROOT, "paper_2605_19945_amd")
     for dirpath, _, files in os.walk(pkg):
