@@ -91,8 +91,8 @@ static __device__ inline int sched_count_mod8(int a, int len, int x) {
 // list, the others the second's (entries tid, + 256 * workgroups of the list, ...).  What bounds a build is the chain
 // of dependent integer work in one thread -- cap, pieces, scans, then divisions and a binary search per entry -- and
 // the two lists have nothing in common but the totals, so no workgroup walks both chains:
-// dispatch launch of the layer 10.3 -> 7.0 us at 1 to 64 tokens (Mixtral shape, 128 small experts), 13.3 -> 9.7 us at
-// 2048 tokens of an expert-parallel share, stand-alone build 12.4 -> 8.6 us.
+// dispatch launch of the layer 10.4 -> 7.1 us (Mixtral shape, 1 token), 11.3 -> 7.6 (128 small experts, 77 tokens),
+// 13.6 -> 9.7 (expert-parallel share, 2048 tokens); stand-alone build 11.0 -> 7.6 (16 wide experts, 3001 tokens).
 // s_off: the exclusive prefix of the experts' rows, [E_local + 1] entries in SHARED memory, written by the caller and
 // published by a barrier before the call.  All 256 threads of the workgroup must call.
 static __device__ inline void schedule_tables(const SchedArgs& a, const int32_t* s_off, int part, int parts) {
@@ -117,137 +117,133 @@ static __device__ inline void schedule_tables(const SchedArgs& a, const int32_t*
         const int h = hmax - c;
         tot[c + 1] = (h >= hmin && nblk_e > 0) ? (nblk_e + h - 1) / h : 0;
     }
-    {
 #pragma unroll
-        for (int c = 0; c < SCHED_CAPS + 2; ++c) {
-            const int incl = wave_scan_incl(tot[c]);
-            if (lane == 63) s_tot[c][wave] = incl;
+    for (int c = 0; c < SCHED_CAPS + 2; ++c) {
+        const int incl = wave_scan_incl(tot[c]);
+        if (lane == 63) s_tot[c][wave] = incl;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < SCHED_CAPS + 2; ++c) tot[c] = s_tot[c][0] + s_tot[c][1] + s_tot[c][2] + s_tot[c][3];
+
+    const bool which = part >= a.parts1;
+    if (which) part -= a.parts1;
+    parts = which ? parts - a.parts1 : a.parts1;
+    const int nt = which ? a.nt2 : a.nt1;
+    const int grid = which ? a.grid2 : a.grid1;
+    TileDesc* table = which ? a.t2 : a.t1;
+    // ---- pick the cap --------------------------------------------------------------------
+    int cap = hmax, MT = 0;
+    float best = 3.0e38f;
+    const int nsplit = which ? a.nsplit2 : a.nsplit1;  // reduction splits: workgroups per table entry
+#pragma unroll
+    for (int c = 0; c < SCHED_CAPS; ++c) {
+        const int tiles = tot[c + 1];
+        if (tiles > 0 && (long long)tiles * nt + 8 <= grid) {
+            const int rounds = (tiles * nt * nsplit + SCHED_CU - 1) / SCHED_CU;
+            const float est = (float)rounds * ((float)tot[0] / (float)tiles + SCHED_TILE_OVERHEAD);
+            if (est < best) {  // ties keep the taller tile
+                best = est;
+                cap = hmax - c;
+                MT = tiles;
+            }
+        }
+    }
+    // ---- pieces and the dense queue of every XCD -------------------------------------------
+    const int mte_mine = (nblk_e + cap - 1) / cap;
+    // second attempt: single-tile pieces, whose queues (at most ceil(MT * nt / 8) long) always fit
+    for (int attempt = 0; attempt < 2; ++attempt) {
+        int cmax = 1;
+        if (attempt == 0) {
+            const long long per64 = (long long)MT * nt / 64;
+            cmax = per64 < 1 ? 1 : (per64 > SCHED_PIECE_MAX ? SCHED_PIECE_MAX : (int)per64);
+        }
+        int pp = (mte_mine + cmax - 1) / cmax;
+        const int pp_incl = block_scan_incl(pp, s_part);
+        int mine[8];
+        if (pp > 0) {
+            // the expert's pieces are S .. S + pp * nt - 1; those of its first prem row ranges are
+            // one tile longer
+            const int S = (pp_incl - pp) * nt, pbase = mte_mine / pp, prem = mte_mine % pp;
+#pragma unroll
+            for (int x = 0; x < 8; ++x)
+                mine[x] = (pbase + 1) * sched_count_mod8(S, prem * nt, x) +
+                          pbase * sched_count_mod8(S + prem * nt, (pp - prem) * nt, x);
+        } else {
+#pragma unroll
+            for (int x = 0; x < 8; ++x) mine[x] = 0;
+        }
+        __syncthreads();  // the previous attempt no longer reads the tables
+        s_mte[tid] = mte_mine;
+        s_pre[tid + 1] = pp_incl;
+        if (tid == 0) s_pre[0] = 0;
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+            mine[x] = wave_scan_incl(mine[x]);
+            if (lane == 63) s_wave[x][wave] = mine[x];
         }
         __syncthreads();
 #pragma unroll
-        for (int c = 0; c < SCHED_CAPS + 2; ++c) tot[c] = s_tot[c][0] + s_tot[c][1] + s_tot[c][2] + s_tot[c][3];
+        for (int x = 0; x < 8; ++x) {
+            int v = mine[x];
+            for (int ww = 0; ww < wave; ++ww) v += s_wave[x][ww];
+            s_len[x][tid + 1] = v;
+            if (tid == 0) s_len[x][0] = 0;
+        }
+        __syncthreads();
+        int longest = 0;
+#pragma unroll
+        for (int x = 0; x < 8; ++x) longest = max(longest, s_len[x][E_local]);
+        if (8 * longest <= grid) break;  // uniform
     }
 
-    {
-        const bool which = part >= a.parts1;
-        if (which) part -= a.parts1;
-        parts = which ? parts - a.parts1 : a.parts1;
-        const int nt = which ? a.nt2 : a.nt1;
-        const int grid = which ? a.grid2 : a.grid1;
-        TileDesc* table = which ? a.t2 : a.t1;
-        // ---- pick the cap --------------------------------------------------------------------
-        int cap = hmax, MT = 0;
-        float best = 3.0e38f;
-        const int nsplit = which ? a.nsplit2 : a.nsplit1;  // reduction splits: workgroups per table entry
-#pragma unroll
-        for (int c = 0; c < SCHED_CAPS; ++c) {
-            const int tiles = tot[c + 1];
-            if (tiles > 0 && (long long)tiles * nt + 8 <= grid) {
-                const int rounds = (tiles * nt * nsplit + SCHED_CU - 1) / SCHED_CU;
-                const float est = (float)rounds * ((float)tot[0] / (float)tiles + SCHED_TILE_OVERHEAD);
-                if (est < best) {  // ties keep the taller tile
-                    best = est;
-                    cap = hmax - c;
-                    MT = tiles;
-                }
+    // Offsets beyond the bound the launches and the buffers were sized for: nothing is scheduled (every
+    // entry stays empty, so no kernel touches a row) and the refusal is recorded for the caller.
+    const bool refused = a.rows_cap >= 0 && s_off[E_local] > a.rows_cap;
+    if (which == 0 && a.refused_out != nullptr && part == 0 && tid == 0) *a.refused_out = refused ? 1 : 0;
+    for (int b = part * 256 + tid; b < grid; b += parts * 256) {
+        const int x = b & 7, j = b >> 3;
+        TileDesc td;
+        td.expert = 0; td.row0 = 0; td.rows = 0; td.n0 = 0;
+        if (!refused && j < s_len[x][E_local]) {
+            // the expert e with s_len[x][e] <= j < s_len[x][e + 1]
+            int lo = 0, hi = E_local;
+            while (hi - lo > 1) {
+                int mid = (lo + hi) >> 1;
+                if (s_len[x][mid] <= j) lo = mid; else hi = mid;
             }
-        }
-        // ---- pieces and the dense queue of every XCD -------------------------------------------
-        const int mte_mine = (nblk_e + cap - 1) / cap;
-        // second attempt: single-tile pieces, whose queues (at most ceil(MT * nt / 8) long) always fit
-        for (int attempt = 0; attempt < 2; ++attempt) {
-            int cmax = 1;
-            if (attempt == 0) {
-                const long long per64 = (long long)MT * nt / 64;
-                cmax = per64 < 1 ? 1 : (per64 > SCHED_PIECE_MAX ? SCHED_PIECE_MAX : (int)per64);
-            }
-            int pp = (mte_mine + cmax - 1) / cmax;
-            const int pp_incl = block_scan_incl(pp, s_part);
-            int mine[8];
-            if (pp > 0) {
-                // the expert's pieces are S .. S + pp * nt - 1; those of its first prem row ranges are
-                // one tile longer
-                const int S = (pp_incl - pp) * nt, pbase = mte_mine / pp, prem = mte_mine % pp;
-#pragma unroll
-                for (int x = 0; x < 8; ++x)
-                    mine[x] = (pbase + 1) * sched_count_mod8(S, prem * nt, x) +
-                              pbase * sched_count_mod8(S + prem * nt, (pp - prem) * nt, x);
+            const int e = lo;
+            const int mte = s_mte[e], pp = s_pre[e + 1] - s_pre[e];
+            const int S = s_pre[e] * nt;
+            const int pbase = mte / pp, prem = mte % pp;
+            // this queue's pieces of the expert: first + 8 i, the long ones come first
+            const int first = S + ((x - S) & 7);
+            const int n_long = sched_count_mod8(S, prem * nt, x);
+            const int r = j - s_len[x][e];
+            int i, pos;
+            if (r < n_long * (pbase + 1)) {
+                i = r / (pbase + 1);
+                pos = r % (pbase + 1);
             } else {
-#pragma unroll
-                for (int x = 0; x < 8; ++x) mine[x] = 0;
+                const int rs = r - n_long * (pbase + 1);
+                i = n_long + rs / pbase;
+                pos = rs % pbase;
             }
-            __syncthreads();  // the tables of the previous attempt or GEMM are no longer read
-            s_mte[tid] = mte_mine;
-            s_pre[tid + 1] = pp_incl;
-            if (tid == 0) s_pre[0] = 0;
-#pragma unroll
-            for (int x = 0; x < 8; ++x) {
-                mine[x] = wave_scan_incl(mine[x]);
-                if (lane == 63) s_wave[x][wave] = mine[x];
-            }
-            __syncthreads();
-#pragma unroll
-            for (int x = 0; x < 8; ++x) {
-                int v = mine[x];
-                for (int ww = 0; ww < wave; ++ww) v += s_wave[x][ww];
-                s_len[x][tid + 1] = v;
-                if (tid == 0) s_len[x][0] = 0;
-            }
-            __syncthreads();
-            int longest = 0;
-#pragma unroll
-            for (int x = 0; x < 8; ++x) longest = max(longest, s_len[x][E_local]);
-            if (8 * longest <= grid) break;  // uniform
+            const int q = first + 8 * i - S;
+            const int pc = q / nt, ni = q % nt;
+            const int mi = pc * pbase + min(pc, prem) + pos;
+            const int e_rows = s_off[e + 1] - s_off[e];
+            // 32-row blocks of the expert, dealt evenly to its mte tiles
+            const int nblk = (e_rows + 31) / 32;
+            const int base = nblk / mte, rem = nblk % mte;
+            const int blk0 = mi * base + min(mi, rem);
+            const int nb = base + (mi < rem ? 1 : 0);
+            td.expert = e;
+            td.row0 = s_off[e] + blk0 * 32;
+            td.rows = min(nb * 32, e_rows - blk0 * 32);
+            td.n0 = ni * a.bn;
         }
-
-        // Offsets beyond the bound the launches and the buffers were sized for: nothing is scheduled (every
-        // entry stays empty, so no kernel touches a row) and the refusal is recorded for the caller.
-        const bool refused = a.rows_cap >= 0 && s_off[E_local] > a.rows_cap;
-        if (which == 0 && a.refused_out != nullptr && part == 0 && tid == 0) *a.refused_out = refused ? 1 : 0;
-        for (int b = part * 256 + tid; b < grid; b += parts * 256) {
-            const int x = b & 7, j = b >> 3;
-            TileDesc td;
-            td.expert = 0; td.row0 = 0; td.rows = 0; td.n0 = 0;
-            if (!refused && j < s_len[x][E_local]) {
-                // the expert e with s_len[x][e] <= j < s_len[x][e + 1]
-                int lo = 0, hi = E_local;
-                while (hi - lo > 1) {
-                    int mid = (lo + hi) >> 1;
-                    if (s_len[x][mid] <= j) lo = mid; else hi = mid;
-                }
-                const int e = lo;
-                const int mte = s_mte[e], pp = s_pre[e + 1] - s_pre[e];
-                const int S = s_pre[e] * nt;
-                const int pbase = mte / pp, prem = mte % pp;
-                // this queue's pieces of the expert: first + 8 i, the long ones come first
-                const int first = S + ((x - S) & 7);
-                const int n_long = sched_count_mod8(S, prem * nt, x);
-                const int r = j - s_len[x][e];
-                int i, pos;
-                if (r < n_long * (pbase + 1)) {
-                    i = r / (pbase + 1);
-                    pos = r % (pbase + 1);
-                } else {
-                    const int rs = r - n_long * (pbase + 1);
-                    i = n_long + rs / pbase;
-                    pos = rs % pbase;
-                }
-                const int q = first + 8 * i - S;
-                const int pc = q / nt, ni = q % nt;
-                const int mi = pc * pbase + min(pc, prem) + pos;
-                const int e_rows = s_off[e + 1] - s_off[e];
-                // 32-row blocks of the expert, dealt evenly to its mte tiles
-                const int nblk = (e_rows + 31) / 32;
-                const int base = nblk / mte, rem = nblk % mte;
-                const int blk0 = mi * base + min(mi, rem);
-                const int nb = base + (mi < rem ? 1 : 0);
-                td.expert = e;
-                td.row0 = s_off[e] + blk0 * 32;
-                td.rows = min(nb * 32, e_rows - blk0 * 32);
-                td.n0 = ni * a.bn;
-            }
-            table[b] = td;
-        }
+        table[b] = td;
     }
 }
 
