@@ -514,11 +514,11 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ 
 // result equals moe_combine on the reduced rows bit for bit and the reduced rows are never written.
 //
 // All slabs of a row are requested before the first is used: one after the other they are NS round trips, and with
-// one token there is nothing else to wait for (Mixtral shape, 1 token, 8 slabs: 6.2 us serial, 4.6 together).  NS is
+// one token there is nothing else to wait for (Mixtral shape, 1 token, 8 slabs: 6.2 us serial, 4.7 together).  NS is
 // a template parameter so that a lane holds 8 * NS registers of partial sums and no more: from a few hundred tokens
 // on the kernel is bound by the bytes its wavefronts keep in flight, and one kernel with room for eight slabs (82
 // registers, 5 wavefronts per SIMD instead of 8) loses there (us, serial / room for eight / this: Mixtral shape, 2
-// slabs, 512 tokens 7.3 / 7.8 / 7.3, 768 tokens 9.9 / 10.8 / 9.9; 16 wide experts, 1000 tokens 9.0 / 9.9 / 8.8).
+// slabs, 512 tokens 7.2 / 7.9 / 7.3, 768 tokens 9.9 / 10.8 / 10.0; 16 wide experts, 1000 tokens 9.0 / 10.0 / 8.8).
 template <int NS>
 __global__ __launch_bounds__(256) void combine_split_kernel(const float* __restrict__ part, size_t slab_elems,
                                                             const int32_t* __restrict__ row_of,

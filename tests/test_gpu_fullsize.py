@@ -20,7 +20,7 @@ import gpu_util as gu
 pytestmark = pytest.mark.gpu
 
 _weights_cache = {}
-ORACLE_FLOP_BUDGET = 8e12      # fp64 flop one oracle evaluation may cost (about 15 s on the GPU machine's host cores)
+ORACLE_FLOP_BUDGET = 8e12      # fp64 flop one oracle evaluation may cost (about 15 s on 16 host cores)
 
 
 def weights_for(key, E_local, d, f):
