@@ -25,18 +25,30 @@
 // So each XCD's queue -- the entries b = x, x + 8, x + 16, ... of the table -- is dense: real tiles
 // only, empty entries follow after the last one.
 //
-// A "piece" is up to SCHED_PIECE_MAX row tiles of one expert and one weight-row tile, consecutive in
-// one XCD's queue: they run side by side and share that weight panel in the XCD's L2.  An expert
-// with more row tiles is cut into pp > 1 row ranges of nearly equal length (the first mte % pp one
-// tile longer).  Pieces are numbered expert-major, then row range, then weight-row tile, and dealt
-// round-robin to the XCDs.  The workgroups resident on one XCD at a time are then consecutive
-// weight-row tiles of one expert times the row tiles of one row range: they share the token panels
-// of that range, all eight XCDs work on the same range (it stays in the Infinity Cache), and every
-// XCD gets its share of every range.  An expert's weights are streamed once per row range.  With few
-// work items the pieces are made shorter so that there are at least 64 of them.
+// Which XCD gets which tiles decides how often a byte crosses the fabric.  What misses an XCD's L2 comes at no
+// more than about 7 TB/s for all eight together, from HBM or out of the Infinity Cache alike (read-only kernel,
+// 64 MB that only that cache holds: 6.9 TB/s), and a single compute unit gets no more than about 60 GB/s of
+// misses against 130 GB/s of hits.  So all tiles stand in one row -- expert by expert; an expert of more than
+// SCHED_PIECE_MAX row tiles in row ranges of nearly equal length; in a range weight-row tile by weight-row tile;
+// the range's row tiles side by side, sharing that weight panel -- and each XCD takes one stretch of an eighth of
+// the row: the token rows of an expert are fetched by one XCD, or by the few that its tiles stretch over.  Dealing
+// the weight-row tiles of every expert round-robin to the XCDs fetches them up to eight times; bytes past the L2,
+// round-robin against stretches: 128 small experts, 8192 tokens 2.31 -> 1.35 and 1.26 -> 0.62 GB (GEMM1, GEMM2),
+// Mixtral shape, 4096 tokens, GEMM2 3.39 -> 1.93 GB, 5003 Zipf-distributed rows of 32 experts 2.51 -> 2.23 and
+// 1.16 -> 1.06 GB.
+//
+// The tiles of a light expert are all weights: each streams a panel that nobody shares, while those of a heavy one
+// find theirs in the L2.  An XCD whose stretch held light experts only would be bound by its share of the
+// fabric while others wait (expert-parallel share, 2048 tokens, one expert with half the rows: 429 us round-robin,
+// 446 in stretches).  So where there are both, the heavy experts (SCHED_HEAVY blocks of 32 rows and more, or
+// several row tiles, which share their weight panels) are cut into stretches and the light ones, whose few token rows cost little to fetch eight times, are dealt round-robin
+// behind them until every XCD holds an eighth of all tiles: 422 us; Zipf-distributed rows 665 -> 652, against 665
+// with the light ones in stretches too; Mixtral shape, 64 tokens, experts of one and two blocks: 381 round-robin, 396 in
+// stretches.  Where no expert has more than one block all tiles cost the same, and they are cut into stretches (Mixtral
+// shape, 1 token: 124.9 against 122.9 us for the layer, 64 tokens 437 against 430).
 // ------------------------------------------------------------------------------------------------
 constexpr int SCHED_CU = 256;    // compute units of the device (one workgroup each)
-constexpr int SCHED_PIECE_MAX = 8;  // row tiles per piece, at most
+constexpr int SCHED_PIECE_MAX = 8;  // row tiles of a row range, at most
 // Per-tile cost that does not scale with the tile's height, in 32-row blocks of MFMA work.  In launches
 // where every row tile has the same height and the workgroups run in step the cost is about one block
 // (Mixtral shape, tiles forced to 6, 7, 8, 9 blocks: 28 rounds of GEMM1 take 2331, 2656, 2993, 3333 us).
@@ -44,17 +56,18 @@ constexpr int SCHED_PIECE_MAX = 8;  // row tiles per piece, at most
 // further the workgroups drift apart -- and 3.5 picks caps that are as fast or up to 2 % faster than
 // those picked with 1.0 on every benchmark workload.
 constexpr float SCHED_TILE_OVERHEAD = 3.5f;
+// 32-row blocks from which an expert is heavy: with more than 96 token rows against the 256 weight rows of a work item,
+// fetching the token rows eight times shows
+constexpr int SCHED_HEAVY = 4;
 constexpr int SCHED_CAPS = 6;  // candidate caps: the tallest tile and the next five heights down
 static __host__ __device__ inline int sched_min_cap_blocks(int bm) {
     const int h = bm / 32 - (SCHED_CAPS - 1);
     return h < 1 ? 1 : h;
 }
 // Entries of a work list (= workgroups of the launch) for at most mt row tiles: the eight queues together
-// hold (row tiles * weight-row tiles) entries; dealing whole pieces can leave them unequal, and the
-// scheduler falls back to single-tile pieces, whose queues differ by at most one entry, when eight times
-// the longest would not fit.  Workgroups past the end of their queue exit at once, but each still has to
-// be placed on a compute unit with its full LDS and register allotment (about 0.5 us): the list is kept
-// as short as the bound allows.
+// hold (row tiles * weight-row tiles) entries and differ by at most one.  Workgroups
+// past the end of their queue exit at once, but each still has to be placed on a compute unit with its full LDS
+// and register allotment (about 0.5 us): the list is kept as short as the bound allows.
 static inline int sched_grid(int mt, int nt) { return mt * nt + 64; }
 
 // inclusive prefix sum over the 64 lanes with data-parallel-primitive moves: a Kogge-Stone scan inside
@@ -82,9 +95,24 @@ static __device__ inline int block_scan_incl(int v, int32_t* part) {
     return v;
 }
 
-// Number of integers in [a, a + len) that are congruent to x modulo 8 (a >= 0, 0 <= x < 8)
-static __device__ inline int sched_count_mod8(int a, int len, int x) {
-    return ((a + len - 1 - x) >> 3) - ((a - 1 - x) >> 3);  // arithmetic shifts: floor division
+// Which tile entry b of a work list is: the light tiles, 0 .. n_light - 1, and the heavy ones, 0 .. total - n_light - 1,
+// are numbered apart.  XCD x = b % 8 has an eighth of all tiles in its queue (rounded by where the eighths begin), first
+// its stretch of the heavy ones, then the light ones x, x + 8, ...; the up to seven light ones left over go to the
+// first XCDs that have room for one more.  -1: past the end of the queue.
+static __host__ __device__ inline int sched_entry(int total, int n_light, int b, bool* light) {
+    const int x = b & 7, j = b >> 3;
+    auto cut = [&](int y) { return (total >> 3) * y + ((total & 7) * y >> 3); };  // total * y / 8
+    const int each = n_light >> 3, left = n_light & 7;
+    const int len = cut(x + 1) - cut(x);
+    // XCDs before x with room for more than `each` light tiles
+    const int rank = (total >> 3) > each ? x : cut(x) - each * x;
+    const int lights = each + (len > each && rank < left ? 1 : 0);
+    *light = false;
+    if (j >= len) return -1;
+    if (j < len - lights) return cut(x) - each * x - (rank < left ? rank : left) + j;
+    *light = true;
+    const int jl = j - (len - lights);
+    return jl < each ? 8 * jl + x : 8 * each + rank;
 }
 
 // Builds this workgroup's share of the work lists: of `parts` workgroups the first a.parts1 build the first GEMM's
@@ -96,10 +124,7 @@ static __device__ inline int sched_count_mod8(int a, int len, int x) {
 // s_off: the exclusive prefix of the experts' rows, [E_local + 1] entries in SHARED memory, written by the caller and
 // published by a barrier before the call.  All 256 threads of the workgroup must call.
 static __device__ inline void schedule_tables(const SchedArgs& a, const int32_t* s_off, int part, int parts) {
-    __shared__ int32_t s_mte[256];     // row tiles of expert e
-    __shared__ int32_t s_pre[257];     // pieces per weight-row tile of the experts before e; [E_local] = total
-    __shared__ int32_t s_len[8][257];  // tiles in XCD x's queue before those of expert e; [E_local] = length
-    __shared__ int32_t s_wave[8][4];
+    __shared__ int32_t s_pre[2][257];  // row tiles of the heavy (0) and light (1) experts before e; [E_local] = all
     __shared__ int32_t s_part[4];
     __shared__ int32_t s_tot[SCHED_CAPS + 2][4];
     const int tid = threadIdx.x;
@@ -133,7 +158,7 @@ static __device__ inline void schedule_tables(const SchedArgs& a, const int32_t*
     const int grid = which ? a.grid2 : a.grid1;
     TileDesc* table = which ? a.t2 : a.t1;
     // ---- pick the cap --------------------------------------------------------------------
-    int cap = hmax, MT = 0;
+    int cap = hmax;
     float best = 3.0e38f;
     const int nsplit = which ? a.nsplit2 : a.nsplit1;  // reduction splits: workgroups per table entry
 #pragma unroll
@@ -145,93 +170,55 @@ static __device__ inline void schedule_tables(const SchedArgs& a, const int32_t*
             if (est < best) {  // ties keep the taller tile
                 best = est;
                 cap = hmax - c;
-                MT = tiles;
             }
         }
     }
-    // ---- pieces and the dense queue of every XCD -------------------------------------------
+    // ---- the heavy experts' tiles in one row, the light ones' in another ----------------------
     const int mte_mine = (nblk_e + cap - 1) / cap;
-    // second attempt: single-tile pieces, whose queues (at most ceil(MT * nt / 8) long) always fit
-    for (int attempt = 0; attempt < 2; ++attempt) {
-        int cmax = 1;
-        if (attempt == 0) {
-            const long long per64 = (long long)MT * nt / 64;
-            cmax = per64 < 1 ? 1 : (per64 > SCHED_PIECE_MAX ? SCHED_PIECE_MAX : (int)per64);
-        }
-        int pp = (mte_mine + cmax - 1) / cmax;
-        const int pp_incl = block_scan_incl(pp, s_part);
-        int mine[8];
-        if (pp > 0) {
-            // the expert's pieces are S .. S + pp * nt - 1; those of its first prem row ranges are
-            // one tile longer
-            const int S = (pp_incl - pp) * nt, pbase = mte_mine / pp, prem = mte_mine % pp;
-#pragma unroll
-            for (int x = 0; x < 8; ++x)
-                mine[x] = (pbase + 1) * sched_count_mod8(S, prem * nt, x) +
-                          pbase * sched_count_mod8(S + prem * nt, (pp - prem) * nt, x);
-        } else {
-#pragma unroll
-            for (int x = 0; x < 8; ++x) mine[x] = 0;
-        }
-        __syncthreads();  // the previous attempt no longer reads the tables
-        s_mte[tid] = mte_mine;
-        s_pre[tid + 1] = pp_incl;
-        if (tid == 0) s_pre[0] = 0;
-#pragma unroll
-        for (int x = 0; x < 8; ++x) {
-            mine[x] = wave_scan_incl(mine[x]);
-            if (lane == 63) s_wave[x][wave] = mine[x];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int x = 0; x < 8; ++x) {
-            int v = mine[x];
-            for (int ww = 0; ww < wave; ++ww) v += s_wave[x][ww];
-            s_len[x][tid + 1] = v;
-            if (tid == 0) s_len[x][0] = 0;
-        }
-        __syncthreads();
-        int longest = 0;
-#pragma unroll
-        for (int x = 0; x < 8; ++x) longest = max(longest, s_len[x][E_local]);
-        if (8 * longest <= grid) break;  // uniform
-    }
-
+    const bool alike = !__syncthreads_or(nblk_e > 1);  // no expert has more than one block
+    const bool heavy_mine = alike || nblk_e >= SCHED_HEAVY || mte_mine > 1;
+    const int incl_h = block_scan_incl(heavy_mine ? mte_mine : 0, s_part);
+    const int incl_l = block_scan_incl(heavy_mine ? 0 : mte_mine, s_part);
+    s_pre[0][tid + 1] = incl_h;
+    s_pre[1][tid + 1] = incl_l;
+    if (tid < 2) s_pre[tid][0] = 0;
+    __syncthreads();
+    const int n_light = s_pre[1][E_local] * nt, total = s_pre[0][E_local] * nt + n_light;
     // Offsets beyond the bound the launches and the buffers were sized for: nothing is scheduled (every
     // entry stays empty, so no kernel touches a row) and the refusal is recorded for the caller.
     const bool refused = a.rows_cap >= 0 && s_off[E_local] > a.rows_cap;
     if (which == 0 && a.refused_out != nullptr && part == 0 && tid == 0) *a.refused_out = refused ? 1 : 0;
     for (int b = part * 256 + tid; b < grid; b += parts * 256) {
-        const int x = b & 7, j = b >> 3;
         TileDesc td;
         td.expert = 0; td.row0 = 0; td.rows = 0; td.n0 = 0;
-        if (!refused && j < s_len[x][E_local]) {
-            // the expert e with s_len[x][e] <= j < s_len[x][e + 1]
+        bool light;
+        const int g = sched_entry(total, n_light, b, &light);  // index among the heavy, or the light, tiles
+        if (!refused && g >= 0) {
+            const int32_t* pre = s_pre[light ? 1 : 0];
+            // the expert e with pre[e] * nt <= g < pre[e + 1] * nt
             int lo = 0, hi = E_local;
             while (hi - lo > 1) {
                 int mid = (lo + hi) >> 1;
-                if (s_len[x][mid] <= j) lo = mid; else hi = mid;
+                if (pre[mid] * nt <= g) lo = mid; else hi = mid;
             }
             const int e = lo;
-            const int mte = s_mte[e], pp = s_pre[e + 1] - s_pre[e];
-            const int S = s_pre[e] * nt;
-            const int pbase = mte / pp, prem = mte % pp;
-            // this queue's pieces of the expert: first + 8 i, the long ones come first
-            const int first = S + ((x - S) & 7);
-            const int n_long = sched_count_mod8(S, prem * nt, x);
-            const int r = j - s_len[x][e];
-            int i, pos;
-            if (r < n_long * (pbase + 1)) {
-                i = r / (pbase + 1);
-                pos = r % (pbase + 1);
+            const int mte = pre[e + 1] - pre[e];
+            // its row ranges: pp of them, the first prem one tile longer
+            const int pp = (mte + SCHED_PIECE_MAX - 1) / SCHED_PIECE_MAX, pbase = mte / pp, prem = mte % pp;
+            int r = g - pre[e] * nt;
+            int range, len;
+            if (r < prem * (pbase + 1) * nt) {
+                len = pbase + 1;
+                range = r / (len * nt);
+                r -= range * len * nt;
             } else {
-                const int rs = r - n_long * (pbase + 1);
-                i = n_long + rs / pbase;
-                pos = rs % pbase;
+                r -= prem * (pbase + 1) * nt;
+                len = pbase;
+                range = prem + r / (len * nt);
+                r -= (range - prem) * len * nt;
             }
-            const int q = first + 8 * i - S;
-            const int pc = q / nt, ni = q % nt;
-            const int mi = pc * pbase + min(pc, prem) + pos;
+            const int ni = r / len;
+            const int mi = range * pbase + min(range, prem) + r % len;
             const int e_rows = s_off[e + 1] - s_off[e];
             // 32-row blocks of the expert, dealt evenly to its mte tiles
             const int nblk = (e_rows + 31) / 32;
