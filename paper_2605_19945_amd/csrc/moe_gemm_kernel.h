@@ -24,11 +24,21 @@
 //     into the registers the MFMA reads, two K steps ahead of its use (three register buffers), and the
 //     eight fragments of its 64 weight rows for one K step are 8 KB in a row: one sequential stream per
 //     wavefront (with a stream per row block the weight-streaming launches were 3 to 7 % slower).
-//     The token rows are staged by global_load_lds into an NSX-deep LDS ring (XOR-swizzled 16-byte
+//     The token rows are staged by global_load_lds into a ring of three LDS stages (XOR-swizzled 16-byte
 //     chunks, see swz_of) and every wavefront multiplies ALL rows of the tile by its own 64 weight
-//     rows (1 x 4 wave layout): no weight byte is loaded twice or touches LDS, and the LDS ring is
-//     deep because it only holds the tokens (NSX-1 token stages and two weight stages, about
-//     150 KB per compute unit, are in flight towards L2).
+//     rows (1 x 4 wave layout): no weight byte is loaded twice or touches LDS.
+//   * weights and tokens are requested two K steps ahead, no further.  A compute unit gets no more than about
+//     60 GB/s of what misses the L2 however much it has requested (read-only kernel, one wavefront per SIMD,
+//     8 or 32 KB in flight for each), and where that is the limit the wavefronts never wait for data: they
+//     stand at the next load, which is not accepted (time stamps around the waits: 56 cycles a K step at the
+//     wait for the loads, which is what two stamps cost, of 1400 to 2500).  Requests further ahead only lengthen
+//     the way to the first MFMA of a tile: with up to five K steps of weights in flight 1.9 -> 4.7 us for one
+//     32-row block, 128 small experts, 8192 tokens 674 -> 717 us for the layer; a third token stage alone
+//     687 -> 658, Mixtral shape, 4096 tokens 2156 -> 2101.
+//   * every tile height has code of its own from the first load to the last store (tile_of): sharing the accumulators
+//     and the epilogue between nine K loops keeps registers alive through all of them.  The last K steps
+//     test once per sub-step whether they still request anything, not once per load; together with the scalar base
+//     of the token loads this also compiles in a sixth of the time.
 //   * one wavefront per SIMD (256 threads, up to 512 registers per lane, accumulators in AGPRs),
 //     so all latency hiding is explicit: LDS fragment reads run one MFMA sub-step ahead, the
 //     barrier that publishes stage kt+1 sits before the LAST sub-step of stage kt so that the first
@@ -96,10 +106,10 @@ static __device__ __forceinline__ const f32x4_t& acc_at(const f32x4_t (&acc)[FA]
     return acc[a][t < NA ? t : 0];  // (t >= NA is never reached at run time: fewer than nine valid blocks)
 }
 
-template <int FT, int FA, int TM, int TN, int EPI, bool NINE>
+template <int FT, int FA, int TN, int EPI, bool NINE>
 static __device__ inline void gemm_epilogue(const f32x4_t (&acc_)[FA][AccShape<FT>::NA],
                                             const f32x4_t (&accv_)[FA][AccShape<FT>::NV], const TileDesc& td, int Np,
-                                            uint16_t* __restrict__ C, int ldc, int wm, int wn, int lane) {
+                                            uint16_t* __restrict__ C, int ldc, int wn, int lane) {
     static_assert(FA == 4 && TN == 64, "wave tile");
     auto A = [&](int a, int t) -> const f32x4_t& {
         return acc_at<NINE, FA, AccShape<FT>::NA, AccShape<FT>::NV>(acc_, accv_, a, t);
@@ -107,7 +117,7 @@ static __device__ inline void gemm_epilogue(const f32x4_t (&acc_)[FA][AccShape<F
     const int frow = lane & 15, fq = lane >> 4;
 #pragma unroll
     for (int t = 0; t < FT; ++t) {
-        const int trow = wm * TM + t * 16 + frow;
+        const int trow = t * 16 + frow;
         if (trow >= td.rows) continue;
         uint16_t* crow = C + (size_t)(td.row0 + trow) * ldc;
         const int prow = td.n0 + wn * TN;  // first packed weight row of this wavefront (Np is a multiple of 64)
@@ -178,7 +188,6 @@ static __device__ inline void gemm_epilogue_staged(const f32x4_t (&acc_)[FA][Acc
     auto swz = [](int r) { return EPI == EPI_SWIGLU ? (r >> 2) & 3 : (r ^ (r >> 3)) & 7; };
 #pragma unroll
     for (int t = 0; t < FT; ++t) {
-        if (t * 16 >= td.rows) break;  // uniform
         const int r = t * 16 + frow;
         // the lane's 4 columns of block a start at byte 32*a + 8*fq of the row: chunk 2*a + fq/2, half fq%2
         char* srow = stage + r * ROWB + 8 * (fq & 1);
@@ -241,6 +250,12 @@ static __device__ inline void wait_lgkmcnt() {
 }
 // makes the fragment "depend" on the preceding wait so that its consumers stay behind it
 static __device__ inline void tie(bf16x8_t& f) { asm volatile("" : "+v"(f)); }
+// the lane index, computed where it is asked for: the compiler can neither merge two of these nor move one
+static __device__ inline int fresh_lane() {
+    int lane;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(lane));
+    return lane;
+}
 
 template <int N>
 static __device__ inline void wait_vmcnt() {
@@ -275,16 +290,9 @@ static __device__ inline void mfma_pinned_agpr(f32x4_t& acc, const bf16x8_t& w, 
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(x));
 }
 
-// s_waitcnt vmcnt(n) for a wave-uniform run-time n (the instruction takes an immediate)
-static __device__ inline void wait_vmcnt_rt(int n) {
-    switch (n) {
-#define C(i) case i: wait_vmcnt<i>(); break;
-        C(1) C(2) C(3) C(4) C(5) C(6) C(7) C(8) C(9) C(10) C(11) C(12) C(13) C(14) C(15) C(16) C(17) C(18)
-        C(19) C(20) C(21) C(22) C(23) C(24) C(25) C(26) C(27) C(28) C(29) C(30) C(31) C(32)
-#undef C
-        default: wait_vmcnt<0>(); break;
-    }
-}
+// LDS of a workgroup: three stages of BM token rows of 128 bytes, or the staged output, BM rows of up to 128 bytes for
+// each wavefront
+static constexpr int gemm_lds_bytes(int bm, int nw) { return bm * 128 * (nw > 3 ? nw : 3); }
 
 // Split K (gridDim.y > 1, used by the router-logit GEMM whose output is tiny next to its reduction
 // length): workgroup (x, y) reduces over elements [y*K, (y+1)*K) of the K_total = gridDim.y * K long
@@ -296,29 +304,27 @@ static __device__ inline void wait_vmcnt_rt(int n) {
 // panels through the L2 lose with the hint (Mixtral shape, 1024 rows per expert: +2.8 % time), so it is a
 // variant picked per launch.
 // gemm_tile: one work item (table entry bx) by one workgroup.
-template <int BM, int NSX, int EPI, int NW, bool W_STREAM>
+template <int BM, int EPI, int NW, bool W_STREAM>
 static __device__ __forceinline__ void gemm_tile(int bx, const uint16_t* __restrict__ X, int ldx,
                                                  const int32_t* __restrict__ row_map,
                                                  const uint16_t* __restrict__ Wf, int Np, int K,
                                                  uint16_t* __restrict__ C, int ldc,
                                                  const TileDesc* __restrict__ table, size_t c_split_bytes) {
-    constexpr int BN = 64 * NW, BK = 64, TN = BN / NW, FA = TN / 16, FM = BM / 32, FT = 2 * FM;
+    constexpr int BN = 64 * NW, BK = 64, TN = BN / NW, FA = TN / 16, FM = BM / 32;
     constexpr int CH = BK / 8;   // 16-byte chunks per staged token row
     constexpr int RPL = 64 / CH; // rows covered by one wave-level load
     constexpr int XP = 32 / (NW * RPL);  // wave-level token loads of one wavefront per 32-row block
     constexpr int KQ = BK / 32;  // K halves of a K step: one v_mfma_f32_16x16x32_bf16 reduces over 32 elements
     constexpr int KK = 2 * KQ;   // MFMA sub-steps per K step: (K half q, token half th), kk = 2*q + th
-    constexpr int DX = NSX - 1;  // token prefetch distance (K steps)
-    constexpr int WPF = 2;       // weight prefetch distance (K steps); WPF + 1 register buffers
     constexpr int WL = FA * KQ;  // weight loads per lane per K step
-    constexpr int STAGE = BM * CH;            // 16-byte chunks per token stage
+    constexpr int NB = 3, PF = NB - 1;  // weight register buffers and token ring stages; K steps both are requested ahead
+    constexpr int SMEM = gemm_lds_bytes(BM, NW);
     constexpr int BLK = 16 * CH * 16;         // bytes between consecutive 16-row blocks in a stage
     static_assert(FA == 4 && KK == 4, "wave tile");
     static_assert(BM % 32 == 0 && FM >= 1 && FM <= 9, "row tile");
     static_assert(NW == 4 || NW == 2, "wavefronts per workgroup");
-    static_assert(NSX >= 3 && (2 * FM * XP + WL) <= 48, "pipeline depth");
 
-    extern __shared__ u32x4_t lds[];  // [NSX][STAGE]
+    extern __shared__ u32x4_t lds[];  // token ring: [stages][rows][CH]
 
     const TileDesc td = table[bx];
     if (td.rows <= 0) return;
@@ -339,10 +345,18 @@ static __device__ __forceinline__ void gemm_tile(int bx, const uint16_t* __restr
 #pragma unroll
     for (int p = 0; p < FM * XP; ++p) {
         const int r = (p * NW + wave) * RPL + lrow;
-        const int rr = r < td.rows ? r : td.rows - 1;  // clamp: rows past the end are never stored
-        int grow = td.row0 + rr;
-        if (row_map != nullptr) grow = row_map[grow];
-        xo[p] = (uint32_t)grow * (uint32_t)(ldx * 2) + (uint32_t)((lphys ^ swz_of<CH>(r)) * 16);
+        xo[p] = (uint32_t)(td.row0 + (r < td.rows ? r : td.rows - 1));  // clamp: rows past the end are never stored
+    }
+    if (row_map != nullptr) {  // (one branch around all the look-ups: they are requested together)
+#pragma unroll
+        for (int p = 0; p < FM * XP; ++p) xo[p] = (uint32_t)row_map[xo[p]];
+    }
+#pragma unroll
+    for (int p = 0; p < FM * XP; ++p) {
+        const int r = (p * NW + wave) * RPL + lrow;
+        // asm: the compiler would use a 64-bit multiply-add, whose result occupies a register pair through the K loop
+        asm("v_mul_lo_u32 %0, %0, %1" : "+v"(xo[p]) : "s"(ldx * 2));
+        xo[p] += (uint32_t)((lphys ^ swz_of<CH>(r)) * 16);
     }
     // weight source: the eight fragments a wavefront needs for one K step (4 row blocks x 2 K halves) are the
     // 8 KB at ((e*Np/64 + nb)*K/64 + kt)*8 KB, fragment j = 4*q + a at j KB: ONE sequential stream per
@@ -351,32 +365,42 @@ static __device__ __forceinline__ void gemm_tile(int bx, const uint16_t* __restr
     int nb = (td.n0 + wave * TN) / 64;
     if (nb >= nbt) nb = nbt - 1;  // past the last weight row: computed, never stored
     const char* wsrc = (const char*)(Wf + ((size_t)td.expert * nbt + nb) * ((size_t)K_total * 64) + (size_t)blockIdx.y * K * 64);
-    const uint32_t wlane = (uint32_t)lane * 16u;
-    // LDS byte address (inside a stage) of this lane's chunk of 16-row block 0 for either K half: token row
-    // frow, reduction elements 32*q + 8*fq .. +8 (the swizzle of a row depends on row % 16 only)
-    uint32_t fx_addr[KQ];
-#pragma unroll
-    for (int q = 0; q < KQ; ++q)
-        fx_addr[q] = (uint32_t)((frow * CH + ((q * 4 + fq) ^ swz_of<CH>(frow))) * 16);
+    // where this wavefront's 1 KB of a pass over a stage goes
+    const uint32_t lds_wave = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds + (uint32_t)wave * (RPL * CH * 16);
 
-    // block (a, t): 16 packed weight rows x 16 token rows (storage: see AccShape)
-    constexpr int NA = AccShape<FT>::NA, NV = AccShape<FT>::NV;
-    f32x4_t acc[FA][NA], accv[FA][NV];
-#pragma unroll
-    for (int a = 0; a < FA; ++a) {
-#pragma unroll
-        for (int t = 0; t < NA; ++t) acc[a][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int t = 0; t < NV; ++t) accv[a][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    }
-
-    auto main_loop = [&](auto fmv_c) {
+    auto tile_of = [&](auto fmv_c) {
         constexpr int FMV = decltype(fmv_c)::value;  // valid 32-row blocks (compile time)
+        constexpr int STAGE = FMV * 32 * CH;         // 16-byte chunks per token stage
+        static_assert(NB * STAGE * 16 <= SMEM, "token ring");
         constexpr int NM = FMV * FA;                 // MFMAs per sub-step: FMV 16-row token blocks x 4 weight blocks
         constexpr int XV = FMV * XP;                 // token loads per lane per K step
         constexpr int NL = WL + XV;                  // loads per lane per K step
 
-        bf16x8_t wr[WPF + 1][KQ][FA];
+        // block (a, t): 16 packed weight rows x 16 token rows (storage: see AccShape)
+        constexpr int FT = 2 * FMV, NA = AccShape<FT>::NA, NV = AccShape<FT>::NV;
+        f32x4_t acc[FA][NA], accv[FA][NV];
+#pragma unroll
+        for (int a = 0; a < FA; ++a) {
+#pragma unroll
+            for (int t = 0; t < NA; ++t) acc[a][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int t = 0; t < NV; ++t) accv[a][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        }
+
+        // The lane's addresses, this height's own: one set of registers for all nine heights would be reloaded from
+        // scratch memory in the K loops of some of them.
+        // fx: LDS byte address (inside a stage) of the lane's chunk of 16-row block 0 for either K half: token row
+        // hl % 16, reduction elements 32*q + 8*(hl/16) .. +8 (the swizzle of a row depends on row % 16 only)
+        const int hl = fresh_lane();
+        const uint32_t wl = (uint32_t)hl * 16u;
+        uint32_t xc[FMV * XP], fx[KQ];
+        static_for<FMV * XP>([&](auto p) { xc[p] = xo[p]; asm volatile("" : "+v"(xc[p])); });
+        static_for<KQ>([&](auto q) {
+            const int row = hl & 15;
+            fx[q] = (uint32_t)((row * CH + ((q * 4 + (hl >> 4)) ^ swz_of<CH>(row))) * 16);
+        });
+
+        bf16x8_t wr[NB][KQ][FA];
         bf16x8_t xf[2][FMV];  // sub-step (q, th): the 16-row token blocks th*FMV .. th*FMV + FMV - 1, K half q
 
         // The tall tiles issue every MFMA through inline asm (see mfma_pinned_agpr).  The compiler then does
@@ -398,11 +422,17 @@ static __device__ __forceinline__ void gemm_tile(int bx, const uint16_t* __restr
             });
         }
 
-        auto issue_x_one = [&](int kt, int p) {
-            u32x4_t* base = lds + (kt % NSX) * STAGE;
-            __builtin_amdgcn_global_load_lds(
-                (const __attribute__((address_space(1))) void*)((const char*)(X + (size_t)kt * BK) + xo[p]),
-                (__attribute__((address_space(3))) void*)(base + (p * NW + wave) * RPL * CH), 16, 0, 0);
+        // token load p of a stage into ring slot `slot`; xbase: the first reduction element of that stage.  Inline asm
+        // for the addressing mode: wave-uniform base plus the lane's 32-bit offset (the builtin keeps a 64-bit address
+        // per load in vector registers and adds to it).  The lanes' 16 bytes land one after the other at M0,
+        // which nothing else in these kernels uses (tests/test_gemm_registers.py).
+        auto issue_x_one = [&](const char* xbase, int slot, int p) {
+            const uint32_t dst = lds_wave + (uint32_t)((slot * STAGE + p * NW * RPL * CH) * 16);
+            const uint32_t off = xc[p];
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                         :
+                         : "s"(dst), "v"(off), "s"(xbase)
+                         : "memory");
         };
         // Weight loads go through inline asm: the compiler's own wait-count pass would otherwise put a
         // nearly-zero vmcnt in front of the MFMAs that consume them (it cannot see through the
@@ -416,46 +446,41 @@ static __device__ __forceinline__ void gemm_tile(int bx, const uint16_t* __restr
             if constexpr (W_STREAM) {
                 asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3 nt"
                              : "=v"(v)
-                             : "v"(wlane), "s"(base), "n"(a * 1024)
+                             : "v"(wl), "s"(base), "n"(a * 1024)
                              : "memory");
             } else {
                 asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3"
                              : "=v"(v)
-                             : "v"(wlane), "s"(base), "n"(a * 1024)
+                             : "v"(wl), "s"(base), "n"(a * 1024)
                              : "memory");
             }
             wr[BUF][kk][a] = __builtin_bit_cast(bf16x8_t, v);
         };
-        // prologue: weights of stages 0, 1 and tokens of stages 0 .. DX-1, oldest needs first
-        static_for<WL>([&](auto j) { load_w_one(0, std::integral_constant<int, 0>{}, j); });
-        static_for<XV>([&](auto p) { issue_x_one(0, p); });
-        int after0 = 0;  // loads issued after those of stage 0
-        if (1 < KT) {
-            static_for<WL>([&](auto j) { load_w_one(1, std::integral_constant<int, 1>{}, j); });
-            after0 += WL;
-        }
-#pragma unroll
-        for (int s = 1; s < DX; ++s)
-            if (s < KT) {
-                static_for<XV>([&](auto p) { issue_x_one(s, p); });
-                after0 += XV;
+        // prologue: stages 0 and 1, each stage's weights and tokens together so that what is needed first is oldest
+        static_for<PF>([&](auto v_c) {
+            constexpr int v = decltype(v_c)::value;
+            if (v < KT) {
+                static_for<WL>([&](auto j) { load_w_one(v, v_c, j); });
+                static_for<XV>([&](auto p) { issue_x_one((const char*)X + v * (BK * 2), v, p); });
             }
-        wait_vmcnt_rt(after0);
+        });
+        if (KT > 1) wait_vmcnt<(PF - 1) * NL>();
+        else wait_vmcnt<0>();
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        static_for<FMV>([&](auto b) { xf[0][b] = lds_read_b128<b * BLK>(fx_addr[0]); });  // sub-step (0, 0)
+        static_for<FMV>([&](auto b) { xf[0][b] = lds_read_b128<b * BLK>(fx[0]); });  // sub-step (0, 0)
 
-        // one K step; BUF = kt % (WPF + 1) is a compile-time register-buffer index.  STEADY: the step
-        // is neither among the first nor the last ones, so every prefetch of it exists and nothing
-        // in it is conditional.
+        // one K step; BUF = kt % NB is a compile-time index of register buffer and ring slot.  STEADY: the step is not
+        // among the last ones, so the prefetch of it exists and nothing in it is conditional.
         auto step = [&](int kt, auto buf_c, auto steady_c) {
             constexpr int BUF = decltype(buf_c)::value;
             constexpr bool STEADY = decltype(steady_c)::value;
-            constexpr int NBUF = (BUF + WPF) % (WPF + 1);  // buffer of stage kt + WPF
-            const bool more_w = STEADY || kt + WPF < KT;
-            const bool more_x = STEADY || kt + DX < KT;
+            constexpr int BUF1 = (BUF + 1) % NB, BUFP = (BUF + PF) % NB;  // of the stages kt + 1 and kt + PF
+            const bool more = STEADY || kt + PF < KT;
             const bool next = STEADY || kt + 1 < KT;
-            const uint32_t sbase = (uint32_t)((kt % NSX) * STAGE * 16);
-            const uint32_t nbase = (uint32_t)(((kt + 1) % NSX) * STAGE * 16);
+            const char* xbase = (const char*)(X + (size_t)(kt + PF) * BK);  // of the stage whose tokens are requested
+            uint32_t sbase = (uint32_t)(BUF * STAGE * 16), nbase = (uint32_t)(BUF1 * STAGE * 16);
+            // (opaque: the compiler would otherwise keep the lane addresses of every slot in registers)
+            asm("" : "+s"(sbase), "+s"(nbase));
             // the weights of this stage landed before the barrier that published it
             static_for<WL>([&](auto j) { tie(wr[BUF][decltype(j)::value / FA][decltype(j)::value % FA]); });
             static_for<KK>([&](auto kk_c) {
@@ -464,22 +489,11 @@ static __device__ __forceinline__ void gemm_tile(int bx, const uint16_t* __restr
                 constexpr int q = kk >> 1, th = kk & 1;          // K half, token half of this sub-step
                 constexpr int qn = (kk + 1) >> 1, thn = (kk + 1) & 1;  // of the next one (same K step)
                 if constexpr (kk == KK - 1) {
-                    // publish stage kt+1 before the last sub-step: own loads of stage kt+1 have landed
-                    // (what may stay in flight: the tokens issued one step ago, after the weights of
-                    // stage kt+1, and everything issued during this step), all wavefronts have issued
-                    // and completed every LDS read of stage kt
-                    if constexpr (STEADY) {
-                        wait_vmcnt<WL + 2 * XV>();
-                    } else {
-                        int pending = (more_w ? WL : 0) + (more_x ? XV : 0);
-                        if (kt >= 1) {
-                            pending += kt - 1 + DX < KT ? XV : 0;
-                        } else {
-#pragma unroll
-                            for (int s = 2; s < DX; ++s) pending += s < KT ? XV : 0;  // issued by the prologue
-                        }
-                        if (next) wait_vmcnt_rt(pending);
-                    }
+                    // publish stage kt+1 before the last sub-step: own loads of stage kt+1 have landed (what may
+                    // stay in flight: the stages after it), all wavefronts have issued and completed every LDS read
+                    // of stage kt
+                    if (more) wait_vmcnt<(PF - 1) * NL>();  // stage kt + 2, requested in this step
+                    else if (next) wait_vmcnt<0>();
                     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
                 } else {
                     wait_lgkmcnt<0>();
@@ -504,76 +518,66 @@ static __device__ __forceinline__ void gemm_tile(int bx, const uint16_t* __restr
                     // enough that their latency is covered by the MFMAs of the second half
                     if constexpr (m < FMV) {
                         if constexpr (kk + 1 < KK) {
-                            xf[nxt][m] = lds_read_b128<(thn * FMV + m) * BLK>(sbase + fx_addr[qn]);
+                            xf[nxt][m] = lds_read_b128<(thn * FMV + m) * BLK>(sbase + fx[qn]);
                         } else {
-                            if (next) xf[nxt][m] = lds_read_b128<m * BLK>(nbase + fx_addr[0]);
+                            if (next) xf[nxt][m] = lds_read_b128<m * BLK>(nbase + fx[0]);
                         }
                     }
-                    // the step's NL loads (weights of stage kt+WPF first, then tokens of stage kt+DX)
-                    // are spread evenly over the MFMA slots of all sub-steps but the last: the four
-                    // wavefronts run in lockstep, and bursts of back-to-back loads from all of them
-                    // exceed what the compute unit's one vector-memory pipe takes per cycle
+                    // the step's NL loads (weights of stage kt+PF first, then its tokens) are spread evenly
+                    // over the MFMA slots of all sub-steps but the last: the four wavefronts run in lockstep, and
+                    // bursts of back-to-back loads from all of them exceed what the compute unit's one vector-memory
+                    // pipe takes per cycle.  (In the last steps, where they are conditional, those of a sub-step go
+                    // together: one branch instead of one per load.)
                     if constexpr (kk < KK - 1) {
-                        constexpr int slot = kk * NM + m, S = (KK - 1) * NM;
-                        static_for<NL>([&](auto i_c) {
-                            constexpr int i = decltype(i_c)::value;
-                            if constexpr ((i * S) / NL == slot) {
-                                if constexpr (i < WL) {
-                                    if (more_w) load_w_one(kt + WPF, std::integral_constant<int, NBUF>{}, std::integral_constant<int, i>{});
-                                } else {
-                                    if (more_x) issue_x_one(kt + DX, i - WL);
-                                }
+                        constexpr int S = (KK - 1) * NM, i_slot = kk * NM + m;
+                        constexpr int s0 = STEADY ? i_slot : kk * NM, s1 = STEADY ? i_slot + 1 : (kk + 1) * NM;  // slots
+                        if constexpr (STEADY || m == 0) {
+                            constexpr int i0 = (s0 * NL + S - 1) / S, i1 = (s1 * NL + S - 1) / S;  // loads of these slots
+                            constexpr int iw = i1 < WL ? i1 : WL, ix = i0 > WL ? i0 : WL;
+                            if (more) {
+                                static_for<(i0 < iw ? iw - i0 : 0)>([&](auto j) {
+                                    load_w_one(kt + PF, std::integral_constant<int, BUFP>{}, std::integral_constant<int, i0 + j>{});
+                                });
+                                static_for<(ix < i1 ? i1 - ix : 0)>([&](auto j) { issue_x_one(xbase, BUFP, ix + j - WL); });
                             }
-                        });
+                        }
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 });
             });
         };
-        using T_ = std::true_type;
-        using F_ = std::false_type;
-        using B0 = std::integral_constant<int, 0>;
-        using B1 = std::integral_constant<int, 1>;
-        using B2 = std::integral_constant<int, 2>;
-        static_assert(WPF == 2, "the loops below rotate three weight buffers");
-        // first step, then the steady steps three at a time, then whatever is left (generic)
-        step(0, B0{}, F_{});
-        int kt = 1;
-        for (; kt + 2 + DX < KT; kt += 3) {
-            step(kt, B1{}, T_{});
-            step(kt + 1, B2{}, T_{});
-            step(kt + 2, B0{}, T_{});
-        }
-        for (; kt < KT; kt += 3) {
-            step(kt, B1{}, F_{});
-            if (kt + 1 < KT) step(kt + 1, B2{}, F_{});
-            if (kt + 2 < KT) step(kt + 2, B0{}, F_{});
+        // the steady steps NB at a time, then whatever is left (generic)
+        int kt = 0;
+        for (; kt + NB - 1 + PF < KT; kt += NB)
+            static_for<NB>([&](auto i) { step(kt + i, i, std::true_type{}); });
+        for (; kt < KT; kt += NB)
+            static_for<NB>([&](auto i) {
+                if (kt + i < KT) step(kt + i, i, std::false_type{});
+            });
+
+        // (the epilogue's addresses depend on nothing but the lane: computed ahead of the K loop, once for all heights,
+        // they, or the lane itself, would be kept in registers through it)
+        const int elane = fresh_lane();
+        if constexpr (EPI == EPI_PLAIN || EPI == EPI_SWIGLU) {
+            static_assert(SMEM >= NW * BM * TN * 2, "staged output");
+            // every wavefront has issued and completed its last reads of the token ring
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            gemm_epilogue_staged<FT, FA, BM, TN, EPI, FMV == 9>(acc, accv, td, Np, C, ldc, wave, elane, (char*)lds);
+        } else {
+            gemm_epilogue<FT, FA, TN, EPI, FMV == 9>(acc, accv, td, Np, C, ldc, wave, elane);
         }
     };
 
     switch (fmv) {
 #define CASE(n)                                                        \
     case n:                                                            \
-        if constexpr (n <= FM) main_loop(std::integral_constant<int, (n <= FM ? n : 1)>{}); \
+        if constexpr (n <= FM) tile_of(std::integral_constant<int, (n <= FM ? n : 1)>{}); \
         break;
         CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8) CASE(9)
 #undef CASE
         default: break;
     }
-
-    if constexpr (EPI == EPI_PLAIN || EPI == EPI_SWIGLU) {
-        static_assert(NSX >= 4, "the staged epilogue uses four quarters of BM x 128 bytes");
-        // every wavefront has issued and completed its last reads of the token ring
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        if (FM == 9 && fmv == 9) gemm_epilogue_staged<FT, FA, BM, TN, EPI, FM == 9>(acc, accv, td, Np, C, ldc, wave, lane, (char*)lds);
-        else gemm_epilogue_staged<FT, FA, BM, TN, EPI, false>(acc, accv, td, Np, C, ldc, wave, lane, (char*)lds);
-    } else {
-        if (FM == 9 && fmv == 9) gemm_epilogue<FT, FA, BM, TN, EPI, FM == 9>(acc, accv, td, Np, C, ldc, 0, wave, lane);
-        else gemm_epilogue<FT, FA, BM, TN, EPI, false>(acc, accv, td, Np, C, ldc, 0, wave, lane);
-    }
 }
-
-
 
 // ---- per-epilogue instantiation units ----------------------------------------------------------
 // Classes 0 and 1 are the production token-tile classes of ordinary loads (row tiles of up to 128 rows for
@@ -582,29 +586,28 @@ static __device__ __forceinline__ void gemm_tile(int bx, const uint16_t* __restr
 // Class 5: two wavefronts per workgroup, 128 packed weight rows and up to 64 token rows per work item.  At a
 // few rows per expert the kernel only streams weights, and what bounds it is the number of bytes a compute
 // unit has in flight: a 4-wavefront workgroup with all its registers keeps 64 KB of weights under way and
-// occupies the compute unit alone; these workgroups need under 256 registers per lane and 33 KB of LDS, four
+// occupies the compute unit alone; these workgroups need under 256 registers per lane and 24 KB of LDS, four
 // of them share a compute unit, together they keep 128 KB under way, and the weight panels are half as large,
 // so a launch has four times as many workgroups to spread over the device (Mixtral shape, 64 tokens: 1792
 // instead of 896 for 256 compute units).
 // A unit that defines MOE_GEMM_NO_TALL_TILE before including this file leaves out the 288-row class (its
 // launcher then rejects class 1): the router-logit GEMM never uses it, and with that unit's epilogue the
 // compiler copies the VGPR accumulators right behind their MFMAs (see mfma_pinned_vgpr).
-//   V(id, BM, NSX, NW)
+//   V(id, BM, NW)
 #ifdef MOE_GEMM_NO_TALL_TILE
 #define FOR_EACH_VARIANT(V) \
-    V(0, 128, 4, 4)         \
-    V(2, 64, 4, 4)          \
-    V(3, 32, 4, 4)          \
-    V(4, 256, 4, 4)         \
-    V(5, 64, 4, 2)
+    V(0, 128, 4)            \
+    V(2, 64, 4)             \
+    V(3, 32, 4)             \
+    V(4, 256, 4)
+static inline int variant_of_class(int cls) { return cls; }
 #else
 #define FOR_EACH_VARIANT(V) \
-    V(0, 128, 4, 4)         \
-    V(1, 288, 4, 4)         \
-    V(2, 64, 4, 4)          \
-    V(3, 32, 4, 4)          \
-    V(4, 256, 4, 4)         \
-    V(5, 64, 4, 2)
+    V(0, 128, 4)            \
+    V(1, 288, 4)            \
+    V(5, 64, 2)
+// The lower tuning classes run on the kernel of the next taller one: a kernel takes tiles of any height up to its own.
+static inline int variant_of_class(int cls) { return cls == 4 ? 1 : (cls == 2 || cls == 3) ? 0 : cls; }
 #endif
 
 // Workgroup x takes the entries x, x + gridDim.x, ... of the work list.  Every class but the decode class is
@@ -615,7 +618,7 @@ static __device__ __forceinline__ void gemm_tile(int bx, const uint16_t* __restr
 // 5 us each): first expert GEMM of the Mixtral shape at 16 rows per expert, 1792 items on 1024 resident
 // workgroups, 310 -> 298 us.  The barrier between two items keeps the next item's token loads out of the ring
 // until every wavefront has read back its staged output.
-template <int BM, int NSX, int EPI, int NW, bool W_STREAM>
+template <int BM, int EPI, int NW, bool W_STREAM>
 __global__ __launch_bounds__(NW * 64) void grouped_gemm_kernel(const uint16_t* __restrict__ X, int ldx,
                                                                const int32_t* __restrict__ row_map,
                                                                const uint16_t* __restrict__ Wf, int Np, int K,
@@ -624,7 +627,7 @@ __global__ __launch_bounds__(NW * 64) void grouped_gemm_kernel(const uint16_t* _
                                                                size_t c_split_bytes, int n_entries) {
     if constexpr (NW == 2) {
         for (int b = blockIdx.x; b < n_entries; b += gridDim.x) {
-            gemm_tile<BM, NSX, EPI, NW, W_STREAM>(b, X, ldx, row_map, Wf, Np, K, C, ldc, table, c_split_bytes);
+            gemm_tile<BM, EPI, NW, W_STREAM>(b, X, ldx, row_map, Wf, Np, K, C, ldc, table, c_split_bytes);
             // LDS reads only: the output stores need not have completed (a full __syncthreads() would also
             // wait for them, and a workgroup that waits for its last stores holds its compute unit longer)
             if (b + (int)gridDim.x < n_entries) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -632,15 +635,15 @@ __global__ __launch_bounds__(NW * 64) void grouped_gemm_kernel(const uint16_t* _
     } else {
         // no loop in the code of the other classes: the compiler would keep the lane-dependent values it can
         // hoist out of it in registers for the whole kernel, and the tall tiles have none to spare
-        gemm_tile<BM, NSX, EPI, NW, W_STREAM>(blockIdx.x, X, ldx, row_map, Wf, Np, K, C, ldc, table, c_split_bytes);
+        gemm_tile<BM, EPI, NW, W_STREAM>(blockIdx.x, X, ldx, row_map, Wf, Np, K, C, ldc, table, c_split_bytes);
     }
 }
 
-template <int BM, int NSX, int EPI, int NW, bool WS>
+template <int BM, int EPI, int NW, bool WS>
 struct Variant {
-    static constexpr size_t smem = (size_t)NSX * BM * 64 * 2;
+    static constexpr size_t smem = gemm_lds_bytes(BM, NW);
     static hipError_t set_attr() {
-        return hipFuncSetAttribute((const void*)grouped_gemm_kernel<BM, NSX, EPI, NW, WS>,
+        return hipFuncSetAttribute((const void*)grouped_gemm_kernel<BM, EPI, NW, WS>,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     }
     // K is the reduction length of ONE split; nsplit = 1 for the expert GEMMs
@@ -649,7 +652,7 @@ struct Variant {
                              size_t c_split_bytes, hipStream_t st) {
         constexpr int RESIDENT = 256 * 4;  // decode class: four workgroups fit a compute unit
         const int gx = (NW == 2 && grid > RESIDENT) ? RESIDENT : grid;
-        hipLaunchKernelGGL((grouped_gemm_kernel<BM, NSX, EPI, NW, WS>), dim3(gx, nsplit), dim3(NW * 64), smem, st,
+        hipLaunchKernelGGL((grouped_gemm_kernel<BM, EPI, NW, WS>), dim3(gx, nsplit), dim3(NW * 64), smem, st,
                            X, ldx, row_map, Wf, Np, K, C, ldc, table, c_split_bytes, grid);
         return hipGetLastError();
     }
@@ -658,8 +661,8 @@ struct Variant {
 template <int EPI, bool WS>
 static hipError_t gemm_set_attr_all() {
     hipError_t err;
-#define V(id, bm, ns, nw)                               \
-    err = Variant<bm, ns, EPI, nw, WS>::set_attr();     \
+#define V(id, bm, nw)                               \
+    err = Variant<bm, EPI, nw, WS>::set_attr();     \
     if (err != hipSuccess) return err;
     FOR_EACH_VARIANT(V)
 #undef V
@@ -670,10 +673,10 @@ template <int EPI, bool WS>
 static hipError_t gemm_launch_any(int cls, int grid, const uint16_t* X, int ldx, const int32_t* row_map,
                                   const uint16_t* Wf, int Np, int K, uint16_t* C, int ldc, const TileDesc* table,
                                   int nsplit, size_t c_split_bytes, hipStream_t st) {
-    switch (cls) {
-#define V(id, bm, ns, nw)                                                                                     \
+    switch (variant_of_class(cls)) {
+#define V(id, bm, nw)                                                                                     \
     case id:                                                                                                  \
-        return Variant<bm, ns, EPI, nw, WS>::launch(grid, X, ldx, row_map, Wf, Np, K, C, ldc, table, nsplit,  \
+        return Variant<bm, EPI, nw, WS>::launch(grid, X, ldx, row_map, Wf, Np, K, C, ldc, table, nsplit,  \
                                                     c_split_bytes, st);
         FOR_EACH_VARIANT(V)
 #undef V
