@@ -11,6 +11,7 @@ import os
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _LIB_NAME = "libmoe_gfx950.so"
 _lib = None
+torch = None  # set by load_library (the mapping search and the argument checks need neither)
 
 FLAG_STAGE_EVENTS = 1
 STAGE_NAMES = ("route", "permute", "gemm1", "gemm2", "combine")
@@ -81,12 +82,12 @@ def exported_symbols():
 
 def load_library():
     """Loads libmoe_gfx950.so from the package directory.  Raises if it has not been built."""
-    global _lib
+    global _lib, torch
     if _lib is not None:
         return _lib
     # PyTorch ships its own HIP runtime; import it first so that the library binds to that one
     # instance instead of bringing a second runtime into the process.
-    import torch  # noqa: F401
+    import torch
     path = library_path()
     if not os.path.exists(path):
         raise RuntimeError(f"{path} is missing: build it with `python -m paper_2605_19945_amd.build` "
@@ -100,20 +101,21 @@ def load_library():
     return lib
 
 
+# A call's arguments are marshalled as plain integers (argtypes makes pointers of them), and the stream is asked for
+# as the raw handle: building the Stream object of torch.cuda.current_stream() took 3.0 us of the 12 us that a program
+# spent on a small routing call, the handle takes 0.2.
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    import torch
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 class MoEContext:
     """One moe_ctx plus its device workspace.  Methods carry the C entry points' names."""
 
     def __init__(self, T_max, d, f, E, k, e_lo=0, E_local=-1, flags=0, device="cuda:0"):
-        import torch
         self.lib = load_library()
         if E_local < 0:
             E_local = E
@@ -150,18 +152,15 @@ class MoEContext:
             raise MoEError(st, what)
 
     def _empty(self, shape, dtype):
-        import torch
         return torch.empty(shape, dtype=dtype, device=self.device)
 
     # ---- load time -----------------------------------------------------------------------------
     def moe_pack_router(self, Wg):
-        import torch
         rp = self._empty(self.lib.moe_packed_router_bytes(C.byref(self.shape)) // 2, torch.bfloat16)
         self._check(self.lib.moe_pack_router(self._ctx, _ptr(Wg), _ptr(rp), _stream()), "moe_pack_router")
         return rp
 
     def moe_pack_weights(self, W1, W3, W2):
-        import torch
         packed = self._empty(self.lib.moe_packed_weight_bytes(C.byref(self.shape)) // 2, torch.bfloat16)
         self._check(self.lib.moe_pack_weights(self._ctx, _ptr(W1), _ptr(W3), _ptr(W2), _ptr(packed), _stream()),
                     "moe_pack_weights")
@@ -170,7 +169,6 @@ class MoEContext:
     # ---- hot path ------------------------------------------------------------------------------
     def moe_route(self, x, router_packed, bias=None, T=None, idx=None, w=None, counts=None):
         """idx / w / counts: optional caller-provided outputs (e.g. one row of a trace matrix)."""
-        import torch
         T = x.shape[0] if T is None else T
         idx = self._empty((T, self.k), torch.int32) if idx is None else idx
         w = self._empty((T, self.k), torch.float32) if w is None else w
@@ -182,7 +180,6 @@ class MoEContext:
         return idx, w, counts
 
     def moe_permute(self, x, topk_idx, T=None, copy_rows=True):
-        import torch
         T = topk_idx.shape[0] if T is None else T
         cap = max(1, self.rows_capacity(T))
         xp = self._empty((cap, self.d), torch.bfloat16) if copy_rows else None
@@ -196,7 +193,6 @@ class MoEContext:
         return xp, offsets, row_of, tok_of
 
     def moe_grouped_ffn(self, xp, offsets, n_rows_cap, packed, y=None):
-        import torch
         if y is None:
             y = self._empty((max(1, n_rows_cap), self.d), torch.bfloat16)
         self._check(self.lib.moe_grouped_ffn(self._ctx, _ptr(xp), _ptr(offsets), n_rows_cap, _ptr(packed), _ptr(y),
@@ -204,7 +200,6 @@ class MoEContext:
         return y
 
     def moe_combine(self, y, row_of, topk_w, T=None, out=None):
-        import torch
         T = row_of.shape[0] if T is None else T
         if out is None:
             out = self._empty((T, self.d), torch.bfloat16)
@@ -213,7 +208,6 @@ class MoEContext:
         return out
 
     def moe_layer_forward(self, x, router_packed, bias, packed, T=None, out=None, counts_out=None):
-        import torch
         T = x.shape[0] if T is None else T
         if out is None:
             out = self._empty((T, self.d), torch.bfloat16)
@@ -229,7 +223,6 @@ class MoEContext:
 
     def moe_profile_ffn(self, xp, packed, token_counts, warmup=3, iters=20, y=None):
         """Mean milliseconds of the isolated expert kernels at each token count (blocking)."""
-        import torch
         counts = [int(n) for n in token_counts]
         if y is None:
             y = self._empty((max(max(counts, default=0), 1), self.d), torch.bfloat16)
@@ -241,7 +234,6 @@ class MoEContext:
 
     def moe_ffn_refused(self):
         """True if the most recent expert-FFN call on this context refused its offsets (blocks until it is done)."""
-        import torch
         p = C.c_void_p()
         self._check(self.lib.moe_ffn_refused_flag(self._ctx, C.byref(p)), "moe_ffn_refused_flag")
         off = p.value - self.workspace.data_ptr()
@@ -256,7 +248,6 @@ class MoEContext:
 
     def moe_layer_intermediates(self, T):
         """Copies of topk_idx [T,k], topk_w [T,k], offsets [E_local+1], row_of [T,k] of the last layer call."""
-        import torch
         p = [C.c_void_p() for _ in range(4)]
         self._check(self.lib.moe_layer_intermediates(self._ctx, *[C.byref(q) for q in p]), "moe_layer_intermediates")
         base = self.workspace.data_ptr()
@@ -273,7 +264,6 @@ class MoEContext:
 def moe_permute_noalloc(x, topk_idx, E, e_lo=0, E_local=-1, xp=None, offsets=None, row_of=None, tok_of=None):
     """moe_permute without a context (scratch in the library's static device array).  The outputs are
     allocated here unless the caller passes them; the library call itself allocates nothing."""
-    import torch
     lib = load_library()
     T, k = topk_idx.shape
     E_local = E if E_local < 0 else E_local
@@ -307,7 +297,6 @@ def _curve_arrays(curves):
 def moe_measure_mfma_rate(iters_per_wave=2500, launches=5, shape=1):
     """Sustained bf16 MFMA rate (TFLOP/s) of the current device under an MFMA-only load; shape 1: 16x16x32
     (the grouped GEMM's instruction), 0: 32x32x16."""
-    import torch
     lib = load_library()
     out = C.c_float()
     st = lib.moe_measure_mfma_rate_of(shape, iters_per_wave, launches, C.byref(out),
@@ -319,7 +308,6 @@ def moe_measure_mfma_rate(iters_per_wave=2500, launches=5, shape=1):
 
 def moe_measure_hbm_read_rate(buf, nontemporal=True, launches=10):
     """GB/s at which a read-only kernel streams the device tensor `buf` (plain or non-temporal loads)."""
-    import torch
     lib = load_library()
     out = C.c_float()
     st = lib.moe_measure_hbm_read_rate(buf.data_ptr(), buf.numel() * buf.element_size(), 1 if nontemporal else 0,
