@@ -285,7 +285,7 @@ moe_status moe_set_tile_class(moe_ctx* c, int32_t cls) {
 int32_t moe_tile_rows(const moe_ctx* c) {
     if (c == nullptr) return 0;
     int cls = c->forced_cls >= 0 ? c->forced_cls : c->last_cls;
-    if (cls < 0) cls = gemm_pick_class((double)c->s.T_max * c->s.k / c->s.E);
+    if (cls < 0) cls = gemm_pick_class_for((double)c->s.T_max * c->s.k, c->s.E, c->s.E_local, c->s.d, c->s.f);
     return gemm_class_rows(cls);
 }
 
@@ -371,7 +371,7 @@ moe_status moe_grouped_ffn(moe_ctx* c, const void* xp, const int32_t* offsets, i
     if (c == nullptr || n_rows_cap < 0 || n_rows_cap > c->rows_cap) return MOE_ERR_INVALID_ARG;
     if (bad_bf16(xp) || bad_i32(offsets) || bad_bf16(packed) || bad_bf16(y)) return MOE_ERR_INVALID_ARG;
     if (n_rows_cap == 0) return MOE_OK;
-    int cls = c->forced_cls >= 0 ? c->forced_cls : gemm_pick_class((double)n_rows_cap / c->s.E_local);
+    int cls = c->forced_cls >= 0 ? c->forced_cls : gemm_pick_class_for(n_rows_cap, c->s.E_local, c->s.E_local, c->s.d, c->s.f);
     return run_ffn(c, cls, (const uint16_t*)xp, nullptr, offsets, n_rows_cap, (const uint16_t*)packed,
                    (uint16_t*)y, (hipStream_t)stream, nullptr);
 }
@@ -405,7 +405,7 @@ moe_status moe_profile_ffn(moe_ctx* c, const void* xp, const void* packed, void*
         if (rc != MOE_OK) break;
         rc = note_hip(hipStreamSynchronize(st), "hipStreamSynchronize");  // host_off is reused
         if (rc != MOE_OK) break;
-        const int cls = c->forced_cls >= 0 ? c->forced_cls : gemm_pick_class((double)n / E_local);
+        const int cls = c->forced_cls >= 0 ? c->forced_cls : gemm_pick_class_for(n, E_local, E_local, c->s.d, c->s.f);
         for (int r = 0; r < warmup + iters && rc == MOE_OK; ++r) {
             if (r == warmup) rc = note_hip(hipEventRecord(e0, st), "hipEventRecord");
             if (rc == MOE_OK)
@@ -447,7 +447,7 @@ moe_status moe_layer_forward(moe_ctx* c, const void* x, const void* rp, const fl
 
     // everything the host decides is decided before the first launch: tile class, work-list sizes, splits
     const int64_t cap = moe_rows_capacity(&s, T);
-    const int cls = c->forced_cls >= 0 ? c->forced_cls : gemm_pick_class((double)T * s.k / s.E);
+    const int cls = c->forced_cls >= 0 ? c->forced_cls : gemm_pick_class_for((double)T * s.k, s.E, s.E_local, s.d, s.f);
     GemmPlan p = gemm_make_plan(cls, cap, s.E_local, s.d, s.f);
     if (p.grid1 > c->table1_cap || p.grid2 > c->table2_cap) return MOE_ERR_WORKSPACE_TOO_SMALL;
     p.w_stream = gemm_pick_stream(cls, (double)T * s.k / s.E);

@@ -1,5 +1,7 @@
 // Work list, tile classes, plans and launches of the grouped GEMMs (the kernel itself lives in
 // moe_gemm_kernel.h and is instantiated per epilogue in moe_gemm_{swiglu,plain,pairsum,partial}.hip).
+#include <math.h>
+
 #include "moe_internal.h"
 
 #include "moe_schedule.h"
@@ -57,6 +59,32 @@ int gemm_pick_class(double rows_per_expert) {
     // expert stays inside one tile: below 12 rows per expert the 128-row class, up to 24 the decode class.
     if (rows_per_expert < 12.0) return GEMM_LOW;
     return rows_per_expert <= 24.0 ? GEMM_DECODE : GEMM_MAIN;
+}
+
+// The class by mean load, corrected by what else the host knows: n_assigned assignments over E_seen experts, of which
+// E_local are resident.
+//  * Below 12 rows per expert the launch streams weights, and a compute unit gets no more than about 50 GB/s of
+//    them: it takes 140 of the 256 to use what HBM gives.  Where the first GEMM would have fewer work items of 256
+//    packed weight rows than that -- few loaded experts (estimated for assignments spread evenly), narrow f -- the
+//    decode class has twice as many, of half the size.  Layer, us, 128-row class against decode: 128 small experts, 1
+//    and 2 tokens 50.6 / 43.3 and 59.1 / 49.6; share of 32 of 256 experts, 4 and 8 tokens 118.8 / 95.8 and
+//    118.8 / 93.9; 16 wide experts, 1 token 102.7 / 94.4; expert GEMMs alone, 4 and 8 rows 93.8 / 74.7 and
+//    111.8 / 94.1.  With more items than that it goes either way (150 to 250 items: 155.8 / 163.3 to 97.9 / 85.3).
+//  * From 12 to 24 rows per expert the decode class wins where the second GEMM has few work items (Mixtral shape,
+//    64 tokens 453.3 / 441.5; 16 wide experts, 256 tokens 694.2 / 678.2).  With two rounds of them or more it only has
+//    its low tiles, and a hot expert streams its weights once per 64 rows: us, 128-row / 288-row / decode
+//    class, 64 experts top-8, 128 and 192 tokens 765 / 771 / 786 and 783 / 776 / 810; share of 256 experts, 512 tokens
+//    230 / 232 / 276; 32 experts with Zipf loads, 512 and 768 rows 462 / 461 / 491 and 495 / 476 / 525.
+int gemm_pick_class_for(double n_assigned, int E_seen, int E_local, int d, int f) {
+    const double mean = n_assigned / E_seen;
+    const int cls = gemm_pick_class(mean);
+    const int nt1 = (2 * f + GEMM_BN - 1) / GEMM_BN, nt2 = (d + GEMM_BN - 1) / GEMM_BN;
+    if (cls == GEMM_DECODE && E_local * nt2 >= 2 * SCHED_CU) return mean <= 16.0 ? GEMM_LOW : GEMM_MAIN;
+    if (cls == GEMM_LOW && mean <= 4.0) {
+        const double loaded = E_local * (1.0 - pow(1.0 - 1.0 / E_seen, n_assigned));
+        if (loaded * nt1 < 140.0) return GEMM_DECODE;
+    }
+    return cls;
 }
 
 GemmPlan gemm_make_plan(int cls, int64_t n_rows_cap, int E_local, int d, int f) {

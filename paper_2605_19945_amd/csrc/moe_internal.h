@@ -142,6 +142,7 @@ hipError_t launch_combine(const uint16_t* y, const int32_t* row_of, const float*
 
 GemmPlan gemm_make_plan(int cls, int64_t n_rows_cap, int E_local, int d, int f);
 int gemm_pick_class(double expected_rows_per_expert);
+int gemm_pick_class_for(double n_assigned, int E_seen, int E_local, int d, int f);
 int gemm_class_rows(int cls);
 bool gemm_pick_stream(int cls, double expected_rows_per_expert);
 hipError_t gemm_init_attributes();
