@@ -173,15 +173,21 @@ static __device__ inline float wave_topk_softmax(uint32_t (&key)[EPL], int k, in
 }
 
 constexpr int ROUTE_TOK = 16;  // tokens per workgroup = N of the 16x16x32 MFMA
+constexpr int TOPK_SUB = 32;   // sub-counters per expert, picked by workgroup, so that the atomics on one address stay few
 
 // NB: blocks of 16 packed router rows; NW: wavefronts per workgroup (they split the reduction).
+// Counts: every workgroup adds its own to one of TOPK_SUB sub-counters per expert (ws, zero between launches) and takes a
+// ticket (ws[0]) once its additions have returned; the last one folds them into counts[] and leaves all zero -- the
+// ordering argument of route_resident_kernel.  One launch, where the counts had to be zeroed by a launch of their own
+// and all workgroups met on one line of them: consecutive calls, 8 experts, d = 3008, 3 tokens 152.9 -> 113.9 us for a
+// trace of them, 16 experts, d = 4544, 215 tokens 170.9 -> 159.5.
 template <int NB, int NW>
 __global__ __launch_bounds__(NW * 64) void route_kernel(const uint16_t* __restrict__ x,
                                                         const uint16_t* __restrict__ rp,
                                                         const float* __restrict__ bias, int T, int d,
                                                         int E, int k, int32_t* __restrict__ idx,
                                                         float* __restrict__ w,
-                                                        int32_t* __restrict__ counts) {
+                                                        int32_t* __restrict__ counts, int32_t* __restrict__ ws) {
     constexpr int R = NB * 16;
     constexpr int EPL = (R + 63) / 64;  // logits per lane during selection
     extern __shared__ float smem[];
@@ -261,8 +267,28 @@ __global__ __launch_bounds__(NW * 64) void route_kernel(const uint16_t* __restri
     }
     __syncthreads();
     if (counts == nullptr) return;  // the caller counts the assignments itself
+    __shared__ int32_t is_last;
+    int32_t* sub = ws + MOE_ROUTE_WS_SUBCOUNTS;
     for (int e = tid; e < E; e += NW * 64)
-        if (hist[e] != 0) atomicAdd(&counts[e], hist[e]);
+        if (hist[e] != 0) {
+            int old = __hip_atomic_fetch_add(&sub[(blockIdx.x % TOPK_SUB) * E + e], hist[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("" ::"v"(old));  // the addition has been performed once its return value is here
+        }
+    __syncthreads();
+    if (tid == 0) is_last = __hip_atomic_fetch_add(&ws[0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+    for (int e = tid; e < R; e += NW * 64) hist[e] = 0;
+    __syncthreads();
+    if (!is_last) return;
+    for (int i = tid; i < TOPK_SUB * E; i += NW * 64) {
+        const int n = __hip_atomic_load(&sub[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (n != 0) {
+            atomicAdd(&hist[i % E], n);
+            __hip_atomic_store(&sub[i], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    __syncthreads();
+    for (int e = tid; e < E; e += NW * 64) counts[e] = hist[e];
+    if (tid == 0) __hip_atomic_store(&ws[0], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next launch
 }
 
 
@@ -373,7 +399,6 @@ __global__ __launch_bounds__(RR_NW * 64) void route_resident_kernel(
 // per token, same keys and tie-break as route_kernel.  Counts go to TOPK_SUB sub-counters per expert
 // (picked by workgroup) so that the atomics on one address stay few; reduce_counts_kernel folds them
 // into counts[] and leaves them zero for the next call.
-constexpr int TOPK_SUB = 32;
 template <int EPL>
 __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ logits, int ldl, int nsplit,
                                                    const float* __restrict__ bias, int T, int E, int k,
@@ -427,19 +452,14 @@ __global__ __launch_bounds__(256) void reduce_counts_kernel(int32_t* __restrict_
     counts[e] = s;
 }
 
-__global__ void zero_i32_kernel(int32_t* p, int n) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
-}
-
 template <int NB, int NW>
 static hipError_t route_launch_t(const uint16_t* x, const uint16_t* rp, const float* bias, int T, int d,
-                                 int E, int k, int32_t* idx, float* w, int32_t* counts, hipStream_t st) {
+                                 int E, int k, int32_t* idx, float* w, int32_t* counts, int32_t* ws, hipStream_t st) {
     constexpr int R = NB * 16;
     size_t smem = (size_t)(NW * R * ROUTE_TOK + ROUTE_TOK * (R + 1)) * sizeof(float) + R * sizeof(int32_t);
     int blocks = (T + ROUTE_TOK - 1) / ROUTE_TOK;
     hipLaunchKernelGGL((route_kernel<NB, NW>), dim3(blocks), dim3(NW * 64), smem, st, x, rp, bias, T, d, E,
-                       k, idx, w, counts);
+                       k, idx, w, counts, ws);
     return hipGetLastError();
 }
 
@@ -470,16 +490,13 @@ hipError_t launch_route(const uint16_t* x, const uint16_t* rp, const float* bias
         if (counts != nullptr) hipLaunchKernelGGL(reduce_counts_kernel, dim3(1), dim3(256), 0, st, sub, E, counts);
         return hipGetLastError();
     }
-    if (counts != nullptr) hipLaunchKernelGGL(zero_i32_kernel, dim3((E + 255) / 256), dim3(256), 0, st, counts, E);
-    err = hipGetLastError();
-    if (err != hipSuccess) return err;
     int nb = moe_router_rows(E) / 16;
     switch (nb) {
-        case 1: return route_launch_t<1, 16>(x, rp, bias, T, d, E, k, idx, w, counts, st);
-        case 2: return route_launch_t<2, 8>(x, rp, bias, T, d, E, k, idx, w, counts, st);
-        case 4: return route_launch_t<4, 4>(x, rp, bias, T, d, E, k, idx, w, counts, st);
-        case 8: return route_launch_t<8, 4>(x, rp, bias, T, d, E, k, idx, w, counts, st);
-        case 16: return route_launch_t<16, 2>(x, rp, bias, T, d, E, k, idx, w, counts, st);
+        case 1: return route_launch_t<1, 16>(x, rp, bias, T, d, E, k, idx, w, counts, route_ws, st);
+        case 2: return route_launch_t<2, 8>(x, rp, bias, T, d, E, k, idx, w, counts, route_ws, st);
+        case 4: return route_launch_t<4, 4>(x, rp, bias, T, d, E, k, idx, w, counts, route_ws, st);
+        case 8: return route_launch_t<8, 4>(x, rp, bias, T, d, E, k, idx, w, counts, route_ws, st);
+        case 16: return route_launch_t<16, 2>(x, rp, bias, T, d, E, k, idx, w, counts, route_ws, st);
         default: return hipErrorInvalidValue;
     }
 }
