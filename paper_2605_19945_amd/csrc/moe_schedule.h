@@ -30,22 +30,39 @@
 // 64 MB that only that cache holds: 6.9 TB/s), and a single compute unit gets no more than about 60 GB/s of
 // misses against 130 GB/s of hits.  So all tiles stand in one row -- expert by expert; an expert of more than
 // SCHED_PIECE_MAX row tiles in row ranges of nearly equal length; in a range weight-row tile by weight-row tile;
-// the range's row tiles side by side, sharing that weight panel -- and each XCD takes one stretch of an eighth of
-// the row: the token rows of an expert are fetched by one XCD, or by the few that its tiles stretch over.  Dealing
-// the weight-row tiles of every expert round-robin to the XCDs fetches them up to eight times; bytes past the L2,
-// round-robin against stretches: 128 small experts, 8192 tokens 2.31 -> 1.35 and 1.26 -> 0.62 GB (GEMM1, GEMM2),
-// Mixtral shape, 4096 tokens, GEMM2 3.39 -> 1.93 GB, 5003 Zipf-distributed rows of 32 experts 2.51 -> 2.23 and
-// 1.16 -> 1.06 GB.
+// the range's row tiles side by side, sharing that weight panel -- and each XCD takes stretches of that row: the
+// token rows of an expert are fetched by the few XCDs that its tiles stretch over.  Dealing the weight-row tiles of
+// every expert round-robin to the XCDs fetches them up to eight times; bytes past the L2, round-robin against one
+// stretch for each XCD: 128 small experts, 8192 tokens 2.31 -> 1.35 and 1.26 -> 0.62 GB (GEMM1, GEMM2), Mixtral shape,
+// 4096 tokens, GEMM2 3.39 -> 1.93 GB, 5003 Zipf-distributed rows of 32 experts 2.51 -> 2.23 and 1.16 -> 1.06 GB.
+//
+// But nothing is stolen between the queues, and an XCD with one stretch of tall tiles ends late.  So the row is dealt
+// in laps of eight chunks of 2^SCHED_CHUNK_SHIFT tiles, one round of an XCD's compute units (of half and a quarter of
+// that in shorter lists, so that a queue averages over four chunks and more), in the opposite order every other lap:
+// on loads that rise or fall along the row the queues then differ by one chunk's difference in height.  Expert GEMMs,
+// us, one stretch / laps / weight-row tiles round-robin: Mixtral shape, loads of 300 to 130 rows 734 / 678 / 673, four
+// experts of 288 and four of 160 rows 705 / 666 / 666; 16 wide experts, 8192 Zipf-distributed rows 1810 / 1697 /
+// 1709; 64 experts, the first half of 288 and the others of 160 rows 1132 / 1065 / 1079, 160 rising to 288
+// 1123 / 1074 / 1092; 32 experts, 32768 Zipf-distributed rows 2377 / 2265 / 2290; 128 small experts, half of 288 and
+// half of 160 rows 331 / 315 / 375.
+// One stretch stays the better one
+//  * where all work items run side by side (no more of them than compute units);
+//  * where light tiles (below) are more than an eighth: they are bound by the fabric and come last, and it serves
+//    them best when the XCDs do not all reach them at once.  Laps without this line: share of 32 of 256 experts, 8192
+//    and 12000 tokens, 2 to 3 and 4 % slower; Mixtral shape, 700 to 1300 tokens of which two experts get 60 % each,
+//    1 to 2 %; only 16 wide experts with 3001 tokens 2 % faster.  Light ones in among the heavy instead of behind
+//    them: 2 to 8 % slower on most loads;
+//  * where no expert has more than one block: all tiles cost the same.
 //
 // The tiles of a light expert are all weights: each streams a panel that nobody shares, while those of a heavy one
 // find theirs in the L2.  An XCD whose stretch held light experts only would be bound by its share of the
 // fabric while others wait (expert-parallel share, 2048 tokens, one expert with half the rows: 429 us round-robin,
 // 446 in stretches).  So where there are both, the heavy experts (SCHED_HEAVY blocks of 32 rows and more, or
-// several row tiles, which share their weight panels) are cut into stretches and the light ones, whose few token rows cost little to fetch eight times, are dealt round-robin
-// behind them until every XCD holds an eighth of all tiles: 422 us; Zipf-distributed rows 665 -> 652, against 665
-// with the light ones in stretches too; Mixtral shape, 64 tokens, experts of one and two blocks: 381 round-robin, 396 in
-// stretches.  Where no expert has more than one block all tiles cost the same, and they are cut into stretches (Mixtral
-// shape, 1 token: 124.9 against 122.9 us for the layer, 64 tokens 437 against 430).
+// several row tiles, which share their weight panels) are dealt as above and the light ones, whose few token rows
+// cost little to fetch eight times, round-robin behind them until every XCD holds an eighth of all tiles: 422 us;
+// Zipf-distributed rows 665 -> 652, against 665 with the light ones in stretches too; Mixtral shape, 64 tokens, experts
+// of one and two blocks: 381 round-robin, 396 in stretches.  Where no expert has more than one block they are cut into
+// stretches (Mixtral shape, 1 token: 124.9 against 122.9 us for the layer, 64 tokens 437 against 430).
 // ------------------------------------------------------------------------------------------------
 constexpr int SCHED_CU = 256;    // compute units of the device (one workgroup each)
 constexpr int SCHED_PIECE_MAX = 8;  // row tiles of a row range, at most
@@ -59,6 +76,7 @@ constexpr float SCHED_TILE_OVERHEAD = 3.5f;
 // 32-row blocks from which an expert is heavy: with more than 96 token rows against the 256 weight rows of a work item,
 // fetching the token rows eight times shows
 constexpr int SCHED_HEAVY = 4;
+constexpr int SCHED_CHUNK_SHIFT = 5;  // log2 of the tiles in a chunk of the heavy experts' row, from 2048 tiles on
 constexpr int SCHED_CAPS = 6;  // candidate caps: the tallest tile and the next five heights down
 static __host__ __device__ inline int sched_min_cap_blocks(int bm) {
     const int h = bm / 32 - (SCHED_CAPS - 1);
@@ -97,19 +115,32 @@ static __device__ inline int block_scan_incl(int v, int32_t* part) {
 
 // Which tile entry b of a work list is: the light tiles, 0 .. n_light - 1, and the heavy ones, 0 .. total - n_light - 1,
 // are numbered apart.  XCD x = b % 8 has an eighth of all tiles in its queue (rounded by where the eighths begin), first
-// its stretch of the heavy ones, then the light ones x, x + 8, ...; the up to seven light ones left over go to the
-// first XCDs that have room for one more.  -1: past the end of the queue.
-static __host__ __device__ inline int sched_entry(int total, int n_light, int b, bool* light) {
-    const int x = b & 7, j = b >> 3;
+// its heavy ones, then the light ones x, x + 8, ...; the up to seven light ones left over go to the first XCDs that have
+// room for one more.  The heavy ones: whole laps of eight chunks (see SCHED_CHUNK_SHIFT), chunk x of the even laps and
+// 7 - x of the odd ones, then a stretch of what is left; the stretch alone where `alike` or the rule there says so.
+// -1: past the end of the queue.
+static __host__ __device__ inline int sched_entry(int total, int n_light, int b, bool* light, bool alike = false) {
+    const int x = b & 7;
+    int j = b >> 3;
+    *light = false;
+    const int heavy = total - n_light;
+    const int shift = heavy >= 2048 ? SCHED_CHUNK_SHIFT : heavy >= 512 ? SCHED_CHUNK_SHIFT - 1 : SCHED_CHUNK_SHIFT - 2;
+    const int laps = alike || total <= SCHED_CU || 8 * (long long)n_light > total ? 0 : heavy >> (shift + 3);
+    const int dealt = laps << shift;  // tiles each XCD gets in whole laps
+    if (j < dealt) {
+        const int lap = j >> shift, chunk = 8 * lap + (lap & 1 ? 7 - x : x);
+        return (chunk << shift) + (j & ((1 << shift) - 1));
+    }
+    j -= dealt;
+    total -= 8 * dealt;
     auto cut = [&](int y) { return (total >> 3) * y + ((total & 7) * y >> 3); };  // total * y / 8
     const int each = n_light >> 3, left = n_light & 7;
     const int len = cut(x + 1) - cut(x);
     // XCDs before x with room for more than `each` light tiles
     const int rank = (total >> 3) > each ? x : cut(x) - each * x;
     const int lights = each + (len > each && rank < left ? 1 : 0);
-    *light = false;
     if (j >= len) return -1;
-    if (j < len - lights) return cut(x) - each * x - (rank < left ? rank : left) + j;
+    if (j < len - lights) return 8 * dealt + cut(x) - each * x - (rank < left ? rank : left) + j;
     *light = true;
     const int jl = j - (len - lights);
     return jl < each ? 8 * jl + x : 8 * each + rank;
@@ -192,7 +223,7 @@ static __device__ inline void schedule_tables(const SchedArgs& a, const int32_t*
         TileDesc td;
         td.expert = 0; td.row0 = 0; td.rows = 0; td.n0 = 0;
         bool light;
-        const int g = sched_entry(total, n_light, b, &light);  // index among the heavy, or the light, tiles
+        const int g = sched_entry(total, n_light, b, &light, alike);  // index among the heavy, or the light, tiles
         if (!refused && g >= 0) {
             const int32_t* pre = s_pre[light ? 1 : 0];
             // the expert e with pre[e] * nt <= g < pre[e + 1] * nt
