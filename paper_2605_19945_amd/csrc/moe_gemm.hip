@@ -70,16 +70,29 @@ int gemm_pick_class(double rows_per_expert) {
 //    and 2 tokens 50.6 / 43.3 and 59.1 / 49.6; share of 32 of 256 experts, 4 and 8 tokens 118.8 / 95.8 and
 //    118.8 / 93.9; 16 wide experts, 1 token 102.7 / 94.4; expert GEMMs alone, 4 and 8 rows 93.8 / 74.7 and
 //    111.8 / 94.1.  With more items than that it goes either way (150 to 250 items: 155.8 / 163.3 to 97.9 / 85.3).
-//  * From 12 to 24 rows per expert the decode class wins where the second GEMM has few work items (Mixtral shape,
-//    64 tokens 453.3 / 441.5; 16 wide experts, 256 tokens 694.2 / 678.2).  With two rounds of them or more it only has
+//    Of 150 random shapes and loads with 0.2 to 12 rows the rule takes 32, none slower and up to 26 % faster; with 200
+//    items four of twelve more lose 7 to 8 %.
+//  * From 12 to 24 rows per expert the decode class wins where a GEMM has few work items (Mixtral shape,
+//    64 tokens 453.3 / 441.5; 16 wide experts, 256 tokens 694.2 / 678.2).  Where both have enough of them it only has
 //    its low tiles, and a hot expert streams its weights once per 64 rows: us, 128-row / 288-row / decode
 //    class, 64 experts top-8, 128 and 192 tokens 765 / 771 / 786 and 783 / 776 / 810; share of 256 experts, 512 tokens
-//    230 / 232 / 276; 32 experts with Zipf loads, 512 and 768 rows 462 / 461 / 491 and 495 / 476 / 525.
+//    230 / 232 / 276; 32 experts with Zipf loads, 512 and 768 rows 462 / 461 / 491 and 495 / 476 / 525.  Enough are
+//    one and a half rounds of the compute units whose last one they fill (four fifths of all rounds): of 350 random
+//    shapes and loads the decode class is then at most 5 % faster, on average 1 % slower.  Without that line for the
+//    first GEMM it is up to 26 % faster: 32 experts, d = 4032, f = 448 (128 items), 82.4 / 85.4 / 67.8; 64 experts,
+//    d = 2048, f = 512 (256 items, a hot expert of 270 rows) 93 / 101 / 85; 128 experts, d = 2368, f = 320 (384 items)
+//    118.4 / 119.6 / 109.4; 48 experts, d = 3008, f = 1536 (576 items in both) 228 / 230 / 218.
+static bool gemm_fills_rounds(int items) {
+    const int rounds = (items + SCHED_CU - 1) / SCHED_CU;
+    return 2 * items >= 3 * SCHED_CU && 5 * items >= 4 * rounds * SCHED_CU;
+}
+
 int gemm_pick_class_for(double n_assigned, int E_seen, int E_local, int d, int f) {
     const double mean = n_assigned / E_seen;
     const int cls = gemm_pick_class(mean);
     const int nt1 = (2 * f + GEMM_BN - 1) / GEMM_BN, nt2 = (d + GEMM_BN - 1) / GEMM_BN;
-    if (cls == GEMM_DECODE && E_local * nt2 >= 2 * SCHED_CU) return mean <= 16.0 ? GEMM_LOW : GEMM_MAIN;
+    if (cls == GEMM_DECODE && gemm_fills_rounds(E_local * nt1) && gemm_fills_rounds(E_local * nt2))
+        return mean <= 16.0 ? GEMM_LOW : GEMM_MAIN;
     if (cls == GEMM_LOW && mean <= 4.0) {
         const double loaded = E_local * (1.0 - pow(1.0 - 1.0 / E_seen, n_assigned));
         if (loaded * nt1 < 140.0) return GEMM_DECODE;

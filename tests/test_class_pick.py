@@ -10,9 +10,13 @@ LOW, MAIN, DECODE = 0, 1, 5
     # the mean load alone: below 12 rows per expert, up to 24, above
     (11.9 * 8, 8, 8, 4096, 14336, LOW), (96, 8, 8, 4096, 14336, DECODE), (192, 8, 8, 4096, 14336, DECODE),
     (193, 8, 8, 4096, 14336, MAIN), (16, 8, 8, 4096, 14336, LOW),
-    # the second GEMM has two rounds of work items: 32 experts x 16 weight-row tiles, one column less, one tile more
-    (32 * 16, 32, 32, 4096, 512, LOW), (32 * 16 + 1, 32, 32, 4096, 512, MAIN), (32 * 16, 32, 32, 3840, 512, DECODE),
-    (32 * 12, 32, 32, 3841 // 64 * 64 + 64, 512, LOW), (256 * 16, 256, 31, 4096, 512, DECODE),
+    # both GEMMs fill their rounds: 32 experts x 16 weight-row tiles; fewer experts, narrower d, narrower f do not
+    (32 * 16, 32, 32, 4096, 2048, LOW), (32 * 16 + 1, 32, 32, 4096, 2048, MAIN), (32 * 12, 32, 32, 3841 // 64 * 64 + 64, 2048, LOW),
+    (256 * 16, 256, 25, 4096, 2048, DECODE), (32 * 16, 32, 32, 2816, 2048, DECODE), (32 * 16, 32, 32, 4096, 512, DECODE),
+    (32 * 16 + 1, 32, 32, 4096, 512, DECODE), (64 * 20, 64, 64, 2048, 512, DECODE),
+    # one and a half rounds, the last one half empty; 1.75 rounds; 2.25 rounds; 2.5 rounds, both ways round
+    (48 * 13, 48, 48, 4160, 1024, DECODE), (64 * 14, 64, 64, 3712, 896, LOW), (48 * 20, 48, 48, 3008, 1536, DECODE),
+    (64 * 20, 64, 64, 2560, 2048, MAIN), (64 * 20, 64, 64, 4096, 1280, MAIN), (64 * 20, 64, 64, 4096, 1152, DECODE),
     # few items in the first GEMM: loaded experts x 16 weight-row tiles against 140
     (4, 256, 32, 7168, 2048, DECODE), (70, 256, 32, 7168, 2048, DECODE), (100, 256, 32, 7168, 2048, LOW),
     (8, 128, 128, 2048, 768, DECODE), (32, 128, 128, 2048, 768, LOW), (1, 1, 1, 64, 64, DECODE),
