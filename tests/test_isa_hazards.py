@@ -7,18 +7,7 @@ instruction by instruction and following branches: nothing but the next accumula
 result until it has been written (7 wait states after a 4-pass MFMA), and nothing writes an operand of an
 asm MFMA in the wait states right before it.
 """
-import os
 import re
-import shutil
-import subprocess
-import sys
-from concurrent.futures import ThreadPoolExecutor
-
-import pytest
-
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-sys.path.insert(0, ROOT)
-from paper_2605_19945_amd import build as moe_build  # noqa: E402
 
 NEED = 8           # wait states before anything else may touch the result (7 by the ISA tables, one to spare)
 MFMA_PASSES = 4    # v_mfma_f32_16x16x32_bf16; the pipe takes the next MFMA when the previous one has gone through
@@ -141,77 +130,104 @@ def find_late_writers(lines):
     return checked, bad
 
 
-def find_touched_before_arrival(lines, limit=4000):
+_COPIES = ("v_mov_b", "v_accvgpr_", "v_swap", "scratch_store", "buffer_store", "global_store", "flat_store", "ds_write")
+
+
+def find_touched_before_arrival(lines):
     """The weight loads are inline asm too (global_load_dwordx4 between ASMSTART / ASMEND), waited for with
     explicit counts: the compiler does not know that their destination registers are not valid yet and could
-    copy or reuse them.  From every such load, walk forward along the fall-through path (a taken branch is
-    followed, a conditional one is not) until an s_waitcnt whose vmcnt is no larger than the number of
-    vector-memory instructions issued since -- or the next barrier, in front of which the kernel waits with a
-    count it picks at run time -- and flag anything that names a destination register before that.  Returns
-    (loads checked, hazards)."""
-    labels = {}
+    copy or reuse them.  From every such load, walk forward along both sides of every branch to an s_waitcnt whose
+    vmcnt is no larger than the number of vector-memory instructions issued since, and flag what names a
+    destination register before that.  The loads of a K step are in flight across its barrier and landed before the
+    next one, so a path ends at its second barrier; and at the asm that computes the lane anew, which opens the
+    epilogue and the code of another tile height.  Past the first barrier only what copies a destination
+    register is flagged -- moves, also between the register files, and stores, which is what a register allocator puts
+    there: the conditions of the last K steps are not followed, and on paths that cannot be taken the registers are free
+    for other uses.
+    Returns (loads checked, loads followed past a barrier, hazards)."""
+    labels, ins, in_asm = {}, [], False
     for i, l in enumerate(lines):
         m = re.match(r"(\.LBB\d+_\d+):", l)
         if m:
             labels[m.group(1)] = i
-    bad, checked, in_asm = [], 0, False
-    for i, l in enumerate(lines):
-        s = l.strip()
-        if s.startswith(";;#ASMSTART"):
-            in_asm = True
+        p = l.strip()
+        if p.startswith(";;#ASM"):
+            in_asm = p.startswith(";;#ASMSTART")
+        op, ops = _split(p)
+        if not op or op.endswith(":") or p.startswith((";", ".")):
+            ins.append(None)
             continue
-        if s.startswith(";;#ASMEND"):
-            in_asm = False
-            continue
-        op, ops = _split(s)
-        if not in_asm or not op.startswith("global_load_dwordx4"):
+        regs = set()
+        for x in ops:
+            for tok in re.findall(r"[va]\[\d+:\d+\]|\b[va]\d+\b", x):
+                regs |= _regs(tok)
+        copied = regs if "store" in op or op.startswith(("ds_write", "v_swap")) else regs - _regs(ops[0] if ops else "")
+        ins.append((op, copied if op.startswith(_COPIES) else set(), regs, in_asm, p))
+    checked, crossed, bad = 0, 0, []
+    for i, load in enumerate(ins):
+        if load is None or not load[3] or not load[0].startswith("global_load_dwordx4"):
             continue
         checked += 1
-        dst = _regs(ops[0])
-        later, j, steps, seen = 0, i + 1, 0, set()
-        while j < len(lines) and steps < limit:
-            p = lines[j].strip()
-            j += 1
-            if not p or p.startswith(";") or p.startswith("."):
-                continue
-            steps += 1
-            o, oo = _split(p)
-            if o == "s_waitcnt":
-                m = re.search(r"vmcnt\((\d+)\)", p)
-                if m and int(m.group(1)) <= later:
+        dst = _regs(_split(load[4])[1][0])
+        paths, seen, past, found = [(i + 1, 0, 0)], set(), False, None
+        while paths and found is None:
+            j, later, barriers = paths.pop()
+            while j < len(ins):
+                at, j = ins[j], j + 1
+                if at is None:
+                    continue
+                op, copied, regs, asm, p = at
+                if op == "s_waitcnt":
+                    m = re.search(r"vmcnt\((\d+)\)", p)
+                    if m and int(m.group(1)) <= later:
+                        break
+                    continue
+                if op == "s_barrier":
+                    barriers, past = barriers + 1, True
+                    if barriers == 2:
+                        break
+                    continue
+                if op == "s_endpgm" or (asm and op.startswith("v_mbcnt")):
                     break
-                continue
-            if o == "s_barrier":
-                break  # every load is waited for (with a count chosen at run time) before the next barrier
-            touched = set()
-            for x in oo:
-                for tok in re.findall(r"[va]\[\d+:\d+\]|\b[va]\d+\b", x):
-                    touched |= _regs(tok)
-            if touched & dst:
-                bad.append(f"line {j}: names a register of the load at line {i + 1} before it has been waited for: {p}")
-                break
-            if o.startswith(("global_", "buffer_", "scratch_", "flat_")):
-                later += 1
-            if o == "s_endpgm":
-                break
-            if o == "s_branch":
-                if oo[0] in seen:
+                if (regs if barriers == 0 else copied) & dst:
+                    found = f"line {j}: names a register of the load at line {i + 1} before it has been waited for: {p}"
                     break
-                seen.add(oo[0])
-                j = labels[oo[0]]
-    return checked, bad
+                if op.startswith(("global_", "buffer_", "scratch_", "flat_")):
+                    later = min(later + 1, 63)  # the counter's largest value
+                if op == "s_branch":
+                    j = labels[p.split()[1]]
+                    if (j, later, barriers) in seen:
+                        break
+                    seen.add((j, later, barriers))
+                elif op.startswith("s_cbranch"):
+                    for state in ((labels[p.split()[1]], later, barriers), (j, later, barriers)):
+                        if state not in seen:
+                            seen.add(state)
+                            paths.append(state)
+                    break
+        crossed += past
+        if found is not None:
+            bad.append(found)
+    return checked, crossed, bad
 
 
 def test_lint_flags_a_register_used_before_its_load_arrived():
     ld = ["\t;;#ASMSTART", "\tglobal_load_dwordx4 v[10:13], v1, s[2:3] offset:0", "\t;;#ASMEND"]
     other = ["\t;;#ASMSTART", "\tglobal_load_dwordx4 v[20:23], v1, s[2:3] offset:1024", "\t;;#ASMEND"]
     ok = ld + other + ["s_waitcnt vmcnt(1)", "v_mov_b32_e32 v5, v10", "s_endpgm"]
-    assert find_touched_before_arrival(ok)[1] == []
+    assert find_touched_before_arrival(ok) == (2, 0, [])
     early = ld + other + ["v_mov_b32_e32 v5, v10", "s_waitcnt vmcnt(1)", "s_endpgm"]
-    assert len(find_touched_before_arrival(early)[1]) == 1
+    assert len(find_touched_before_arrival(early)[2]) == 1
     third = ["\t;;#ASMSTART", "\tglobal_load_dwordx4 v[30:33], v1, s[2:3] offset:2048", "\t;;#ASMEND"]
     not_enough = ld + other + third + ["s_waitcnt vmcnt(3)", "v_mov_b32_e32 v5, v11", "s_waitcnt vmcnt(0)", "s_endpgm"]
-    assert len(find_touched_before_arrival(not_enough)[1]) == 1
+    assert len(find_touched_before_arrival(not_enough)[2]) == 1
+    # in flight across the barrier: a copy on the taken side of a branch, behind a loop's back edge, or to scratch memory
+    for copy in ("v_mov_b32_e32 v5, v10", "v_accvgpr_write_b32 a7, v11", "scratch_store_dwordx4 off, v[10:13], off"):
+        back = [".LBB0_1:", copy] + ld + ["s_barrier", "s_cbranch_scc1 .LBB0_1", "s_waitcnt vmcnt(0)", "s_endpgm"]
+        side = ld + ["s_barrier", "s_cbranch_scc1 .LBB0_2", "s_waitcnt vmcnt(0)", "s_endpgm", ".LBB0_2:", copy, "s_endpgm"]
+        late = ld + ["s_barrier", "s_waitcnt vmcnt(0)", "s_barrier", copy, "s_endpgm"]
+        assert [len(find_touched_before_arrival(x)[2]) for x in (back, side, late)] == [1, 1, 0], copy
+        assert find_touched_before_arrival(late)[:2] == (1, 1)
 
 
 def test_lint_flags_a_late_writer():
@@ -246,32 +262,13 @@ def test_lint_flags_an_early_reader():
     assert find_hazards(late_agpr, agpr_too=True) == (3, [])
 
 
-@pytest.mark.skipif(shutil.which("hipcc") is None and not os.path.exists("/opt/rocm/bin/hipcc"), reason="no hipcc")
-def test_no_hazard_around_the_mfmas_of_the_compiled_kernels(tmp_path):
-    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
-    units = [u for u in moe_build.SOURCES if u.startswith("moe_gemm_")]   # every unit that instantiates the kernel
-    assert len(units) == 7
-
-    def compile_one(src):
-        out = str(tmp_path / src.replace(".hip", ".s"))
-        r = subprocess.run([hipcc, *moe_build.FLAGS, "-S", "--cuda-device-only", "-o", out,
-                            os.path.join(moe_build.CSRC, src)], capture_output=True, text=True)
-        assert r.returncode == 0, r.stderr[-2000:]
-        return out
-
-    with ThreadPoolExecutor(len(units)) as ex:
-        outs = list(ex.map(compile_one, units))
-    for out in outs:
-        with open(out) as fh:
-            pinned, bad = find_hazards(fh.read().splitlines(), agpr_too=True)
-        if out.endswith("pairsum.s"):
-            assert pinned > 0
-        else:
-            assert pinned > 0, f"{out}: expected MFMAs"
-        assert not bad, f"{out}:\n" + "\n".join(bad[:10])
-        with open(out) as fh:
-            n_asm, late = find_late_writers(fh.read().splitlines())
-        assert not late, f"{out}:\n" + "\n".join(late[:10])
-        with open(out) as fh:
-            n_loads, early = find_touched_before_arrival(fh.read().splitlines())
-        assert n_loads > 0 and not early, f"{out}:\n" + "\n".join(early[:10])
+def test_no_hazard_around_the_mfmas_of_the_compiled_kernels(gemm_unit_asm):
+    assert len(gemm_unit_asm) == 7
+    for unit, lines in gemm_unit_asm.items():
+        pinned, bad = find_hazards(lines, agpr_too=True)
+        assert pinned > 0, f"{unit}: expected MFMAs"
+        assert not bad, f"{unit}:\n" + "\n".join(bad[:10])
+        n_asm, late = find_late_writers(lines)
+        assert not late, f"{unit}:\n" + "\n".join(late[:10])
+        n_loads, crossed, early = find_touched_before_arrival(lines)
+        assert n_loads > 0 and crossed > 0 and not early, f"{unit}:\n" + "\n".join(early[:10])
