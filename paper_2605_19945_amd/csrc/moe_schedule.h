@@ -83,9 +83,9 @@ static __host__ __device__ inline int sched_min_cap_blocks(int bm) {
     return h < 1 ? 1 : h;
 }
 // Entries of a work list (= workgroups of the launch) for at most mt row tiles: the eight queues together
-// hold (row tiles * weight-row tiles) entries and differ by at most one.  Workgroups
-// past the end of their queue exit at once, but each still has to be placed on a compute unit with its full LDS
-// and register allotment (about 0.5 us): the list is kept as short as the bound allows.
+// hold (row tiles * weight-row tiles) entries and differ by at most one, which takes up to 8 more entries than tiles
+// (64 are kept).  Workgroups past the end of their queue exit at once, but each still has to be placed on a compute
+// unit with its full LDS and register allotment (about 0.5 us), so the list follows the bound on the row tiles.
 static inline int sched_grid(int mt, int nt) { return mt * nt + 64; }
 
 // inclusive prefix sum over the 64 lanes with data-parallel-primitive moves: a Kogge-Stone scan inside
@@ -114,11 +114,11 @@ static __device__ inline int block_scan_incl(int v, int32_t* part) {
 }
 
 // Which tile entry b of a work list is: the light tiles, 0 .. n_light - 1, and the heavy ones, 0 .. total - n_light - 1,
-// are numbered apart.  XCD x = b % 8 has an eighth of all tiles in its queue (rounded by where the eighths begin), first
-// its heavy ones, then the light ones x, x + 8, ...; the up to seven light ones left over go to the first XCDs that have
-// room for one more.  The heavy ones: whole laps of eight chunks (see SCHED_CHUNK_SHIFT), chunk x of the even laps and
-// 7 - x of the odd ones, then a stretch of what is left; the stretch alone where `alike` or the rule there says so.
-// -1: past the end of the queue.
+// are numbered apart.  XCD x = b % 8 has an eighth of all tiles in its queue (rounded by where the eighths begin),
+// first its heavy ones, then the light ones x, x + 8, ...; the up to seven light ones left over go to the first XCDs
+// that have room for one more.  The heavy ones: whole laps of eight chunks of 2^SCHED_CHUNK_SHIFT tiles (less in shorter
+// lists), chunk x of the even laps and 7 - x of the odd ones, then a stretch of what is left; the stretch alone where
+// one stretch is the better one (see above; alike: no expert has more than one block).  -1: past the end of the queue.
 static __host__ __device__ inline int sched_entry(int total, int n_light, int b, bool* light, bool alike = false) {
     const int x = b & 7;
     int j = b >> 3;
@@ -146,52 +146,57 @@ static __host__ __device__ inline int sched_entry(int total, int n_light, int b,
     return jl < each ? 8 * jl + x : 8 * each + rank;
 }
 
-// Builds this workgroup's share of the work lists: of `parts` workgroups the first a.parts1 build the first GEMM's
-// list, the others the second's (entries tid, + 256 * workgroups of the list, ...).  What bounds a build is the chain
-// of dependent integer work in one thread -- cap, pieces, scans, then divisions and a binary search per entry -- and
-// the two lists have nothing in common but the totals, so no workgroup walks both chains:
-// dispatch launch of the layer 10.4 -> 7.1 us (Mixtral shape, 1 token), 11.3 -> 7.6 (128 small experts, 77 tokens),
-// 13.6 -> 9.7 (expert-parallel share, 2048 tokens); stand-alone build 11.0 -> 7.6 (16 wide experts, 3001 tokens).
-// s_off: the exclusive prefix of the experts' rows, [E_local + 1] entries in SHARED memory, written by the caller and
-// published by a barrier before the call.  All 256 threads of the workgroup must call.
-static __device__ inline void schedule_tables(const SchedArgs& a, const int32_t* s_off, int part, int parts) {
-    __shared__ int32_t s_pre[2][257];  // row tiles of the heavy (0) and light (1) experts before e; [E_local] = all
-    __shared__ int32_t s_part[4];
-    __shared__ int32_t s_tot[SCHED_CAPS + 2][4];
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int E_local = a.E_local;
-    int nblk_e = 0;  // 32-row blocks of expert tid
-    if (tid < E_local) nblk_e = (s_off[tid + 1] - s_off[tid] + 31) / 32;
-    const int hmax = a.bm / 32, hmin = sched_min_cap_blocks(a.bm);
-    // totals over the experts: 32-row blocks, loaded experts, row tiles for every candidate cap
-    int tot[SCHED_CAPS + 2];
-    tot[0] = nblk_e;
-    tot[SCHED_CAPS + 1] = nblk_e > 0 ? 1 : 0;
-#pragma unroll
-    for (int c = 0; c < SCHED_CAPS; ++c) {
-        const int h = hmax - c;
-        tot[c + 1] = (h >= hmin && nblk_e > 0) ? (nblk_e + h - 1) / h : 0;
+// The tile with index g in the row of tiles of the experts that pre counts (pre[e]: row tiles of those before e,
+// pre[E_local] of all; an expert may have none): expert by expert, row range by row range, weight-row tile by weight-row
+// tile.  s_off: the exclusive prefix of the experts' rows.  0 <= g < pre[E_local] * nt.
+static __host__ __device__ inline TileDesc sched_tile(int g, const int32_t* pre, const int32_t* s_off, int E_local, int nt,
+                                                      int bn) {
+    // the expert e with pre[e] * nt <= g < pre[e + 1] * nt
+    int lo = 0, hi = E_local;
+    while (hi - lo > 1) {
+        int mid = (lo + hi) >> 1;
+        if (pre[mid] * nt <= g) lo = mid; else hi = mid;
     }
-#pragma unroll
-    for (int c = 0; c < SCHED_CAPS + 2; ++c) {
-        const int incl = wave_scan_incl(tot[c]);
-        if (lane == 63) s_tot[c][wave] = incl;
+    const int e = lo;
+    const int mte = pre[e + 1] - pre[e];
+    // its row ranges: pp of them, the first prem one tile longer
+    const int pp = (mte + SCHED_PIECE_MAX - 1) / SCHED_PIECE_MAX, pbase = mte / pp, prem = mte % pp;
+    int r = g - pre[e] * nt;
+    int range, len;
+    if (r < prem * (pbase + 1) * nt) {
+        len = pbase + 1;
+        range = r / (len * nt);
+        r -= range * len * nt;
+    } else {
+        r -= prem * (pbase + 1) * nt;
+        len = pbase;
+        range = prem + r / (len * nt);
+        r -= (range - prem) * len * nt;
     }
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < SCHED_CAPS + 2; ++c) tot[c] = s_tot[c][0] + s_tot[c][1] + s_tot[c][2] + s_tot[c][3];
+    const int ni = r / len;
+    const int mi = range * pbase + (range < prem ? range : prem) + r % len;
+    const int e_rows = s_off[e + 1] - s_off[e];
+    // 32-row blocks of the expert, dealt evenly to its mte tiles
+    const int nblk = (e_rows + 31) / 32;
+    const int base = nblk / mte, rem = nblk % mte;
+    const int blk0 = mi * base + (mi < rem ? mi : rem);
+    const int rows = (base + (mi < rem ? 1 : 0)) * 32, left = e_rows - blk0 * 32;
+    TileDesc td;
+    td.expert = e;
+    td.row0 = s_off[e] + blk0 * 32;
+    td.rows = rows < left ? rows : left;
+    td.n0 = ni * bn;
+    return td;
+}
 
-    const bool which = part >= a.parts1;
-    if (which) part -= a.parts1;
-    parts = which ? parts - a.parts1 : a.parts1;
-    const int nt = which ? a.nt2 : a.nt1;
-    const int grid = which ? a.grid2 : a.grid1;
-    TileDesc* table = which ? a.t2 : a.t1;
-    // ---- pick the cap --------------------------------------------------------------------
+// Whether an expert of nblk 32-row blocks in mte row tiles is heavy
+static __host__ __device__ inline bool sched_heavy(int nblk, int mte) { return nblk >= SCHED_HEAVY || mte > 1; }
+
+// The cap of a launch (tallest row tile, in 32-row blocks) among the SCHED_CAPS from hmax down.  tot: 32-row blocks of all
+// experts, then their row tiles under each candidate (0: none of that height).
+static __host__ __device__ inline int sched_cap(const int* tot, int hmax, int nt, int nsplit, int grid) {
     int cap = hmax;
     float best = 3.0e38f;
-    const int nsplit = which ? a.nsplit2 : a.nsplit1;  // reduction splits: workgroups per table entry
 #pragma unroll
     for (int c = 0; c < SCHED_CAPS; ++c) {
         const int tiles = tot[c + 1];
@@ -204,10 +209,56 @@ static __device__ inline void schedule_tables(const SchedArgs& a, const int32_t*
             }
         }
     }
+    return cap;
+}
+
+// Builds this workgroup's share of the work lists: of `parts` workgroups the first a.parts1 build the first GEMM's
+// list, the others the second's (entries tid, + 256 * workgroups of the list, ...).  What bounds a build is the chain
+// of dependent integer work in one thread -- cap, scans, then divisions and a binary search per entry -- and
+// the two lists have nothing in common but the totals, so no workgroup walks both chains:
+// dispatch launch of the layer 10.4 -> 7.1 us (Mixtral shape, 1 token), 11.3 -> 7.6 (128 small experts, 77 tokens),
+// 13.6 -> 9.7 (expert-parallel share, 2048 tokens); stand-alone build 11.0 -> 7.6 (16 wide experts, 3001 tokens).
+// s_off: the exclusive prefix of the experts' rows, [E_local + 1] entries in SHARED memory, written by the caller and
+// published by a barrier before the call.  All 256 threads of the workgroup must call.
+static __device__ inline void schedule_tables(const SchedArgs& a, const int32_t* s_off, int part, int parts) {
+    __shared__ int32_t s_pre[2][257];  // row tiles of the heavy (0) and light (1) experts before e; [E_local] = all
+    __shared__ int32_t s_part[4];
+    __shared__ int32_t s_tot[SCHED_CAPS + 1][4];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int E_local = a.E_local;
+    int nblk_e = 0;  // 32-row blocks of expert tid
+    if (tid < E_local) nblk_e = (s_off[tid + 1] - s_off[tid] + 31) / 32;
+    const int hmax = a.bm / 32, hmin = sched_min_cap_blocks(a.bm);
+    // totals over the experts: 32-row blocks, row tiles for every candidate cap
+    int tot[SCHED_CAPS + 1];
+    tot[0] = nblk_e;
+#pragma unroll
+    for (int c = 0; c < SCHED_CAPS; ++c) {
+        const int h = hmax - c;
+        tot[c + 1] = (h >= hmin && nblk_e > 0) ? (nblk_e + h - 1) / h : 0;
+    }
+#pragma unroll
+    for (int c = 0; c < SCHED_CAPS + 1; ++c) {
+        const int incl = wave_scan_incl(tot[c]);
+        if (lane == 63) s_tot[c][wave] = incl;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < SCHED_CAPS + 1; ++c) tot[c] = s_tot[c][0] + s_tot[c][1] + s_tot[c][2] + s_tot[c][3];
+
+    const bool which = part >= a.parts1;
+    if (which) part -= a.parts1;
+    parts = which ? parts - a.parts1 : a.parts1;
+    const int nt = which ? a.nt2 : a.nt1;
+    const int grid = which ? a.grid2 : a.grid1;
+    TileDesc* table = which ? a.t2 : a.t1;
+    const int nsplit = which ? a.nsplit2 : a.nsplit1;  // reduction splits: workgroups per table entry
+    const int cap = sched_cap(tot, hmax, nt, nsplit, grid);
     // ---- the heavy experts' tiles in one row, the light ones' in another ----------------------
     const int mte_mine = (nblk_e + cap - 1) / cap;
     const bool alike = !__syncthreads_or(nblk_e > 1);  // no expert has more than one block
-    const bool heavy_mine = alike || nblk_e >= SCHED_HEAVY || mte_mine > 1;
+    const bool heavy_mine = alike || sched_heavy(nblk_e, mte_mine);
     const int incl_h = block_scan_incl(heavy_mine ? mte_mine : 0, s_part);
     const int incl_l = block_scan_incl(heavy_mine ? 0 : mte_mine, s_part);
     s_pre[0][tid + 1] = incl_h;
@@ -224,43 +275,7 @@ static __device__ inline void schedule_tables(const SchedArgs& a, const int32_t*
         td.expert = 0; td.row0 = 0; td.rows = 0; td.n0 = 0;
         bool light;
         const int g = sched_entry(total, n_light, b, &light, alike);  // index among the heavy, or the light, tiles
-        if (!refused && g >= 0) {
-            const int32_t* pre = s_pre[light ? 1 : 0];
-            // the expert e with pre[e] * nt <= g < pre[e + 1] * nt
-            int lo = 0, hi = E_local;
-            while (hi - lo > 1) {
-                int mid = (lo + hi) >> 1;
-                if (pre[mid] * nt <= g) lo = mid; else hi = mid;
-            }
-            const int e = lo;
-            const int mte = pre[e + 1] - pre[e];
-            // its row ranges: pp of them, the first prem one tile longer
-            const int pp = (mte + SCHED_PIECE_MAX - 1) / SCHED_PIECE_MAX, pbase = mte / pp, prem = mte % pp;
-            int r = g - pre[e] * nt;
-            int range, len;
-            if (r < prem * (pbase + 1) * nt) {
-                len = pbase + 1;
-                range = r / (len * nt);
-                r -= range * len * nt;
-            } else {
-                r -= prem * (pbase + 1) * nt;
-                len = pbase;
-                range = prem + r / (len * nt);
-                r -= (range - prem) * len * nt;
-            }
-            const int ni = r / len;
-            const int mi = range * pbase + min(range, prem) + r % len;
-            const int e_rows = s_off[e + 1] - s_off[e];
-            // 32-row blocks of the expert, dealt evenly to its mte tiles
-            const int nblk = (e_rows + 31) / 32;
-            const int base = nblk / mte, rem = nblk % mte;
-            const int blk0 = mi * base + min(mi, rem);
-            const int nb = base + (mi < rem ? 1 : 0);
-            td.expert = e;
-            td.row0 = s_off[e] + blk0 * 32;
-            td.rows = min(nb * 32, e_rows - blk0 * 32);
-            td.n0 = ni * a.bn;
-        }
+        if (!refused && g >= 0) td = sched_tile(g, s_pre[light ? 1 : 0], s_off, E_local, nt, a.bn);
         table[b] = td;
     }
 }

@@ -1,5 +1,6 @@
-"""Expert FFN over rows per expert that mix heavy experts, experts of several row tiles and light ones, at every height of
-a row tile and at the numbers of K steps around the length of the pipeline: all rows against the oracle."""
+"""Expert FFN over rows per expert that mix heavy experts, experts of several row tiles and light ones, and over many
+experts whose row tiles stay whole up to the tallest one, at the numbers of K steps around the length of the pipeline: all
+rows against the oracle."""
 import numpy as np
 import pytest
 
@@ -24,15 +25,17 @@ def _bits(rng, *shape, std=1.0):
     return ((u + 0x7FFF + ((u >> 16) & 1)) >> 16).astype(np.uint16)
 
 
-@pytest.mark.parametrize("cls", [-1, 0, 1, 5])
-@pytest.mark.parametrize("d,f", [(64, 64), (128, 192), (192, 320), (256, 448), (320, 576), (704, 128)])
-@pytest.mark.parametrize("load", sorted(LOADS))
-def test_rows_against_the_oracle(load, d, f, cls):
+# Few work items make the device cut tiles to four blocks and less; 256 experts of five to nine blocks fill whole rounds
+# with uncut ones (test_schedule_entries.py holds the work lists to that).  Last blocks of 1, 19, 31 and 32 rows.
+TALL_ROWS = [32 * (5 + e % 5) - (0, 1, 13, 31)[e // 5 % 4] for e in range(256)]
+TALL_WIDTHS = [(64, 64), (128, 192), (192, 320), (256, 128), (320, 256)]  # one to five K steps in either GEMM
+
+
+def _against_the_oracle(rows, d, f, cls, what):
     import torch
     import paper_2605_19945_amd as moe
-    rows = LOADS[load]
     E, n = len(rows), sum(rows)
-    print(f"load={load} d={d} f={f} cls={cls}", flush=True)
+    print(f"{what} d={d} f={f} cls={cls}", flush=True)
     rng = np.random.default_rng(d + 7 * f + len(rows))
     off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
     xp = _bits(rng, n, d)
@@ -46,4 +49,16 @@ def test_rows_against_the_oracle(load, d, f, cls):
     ctx.close()
     # one rounding of the intermediate and one of the result, bounded as in the other parity tests; a row that no work
     # item holds stays NaN
-    gu.check_output(gu.f64_of_bf16(y), orc.grouped_ffn(xp, off, W1, W3, W2), what=f"{load} d={d} f={f} cls={cls}")
+    gu.check_output(gu.f64_of_bf16(y), orc.grouped_ffn(xp, off, W1, W3, W2), what=f"{what} d={d} f={f} cls={cls}")
+
+
+@pytest.mark.parametrize("cls", [-1, 0, 1, 5])
+@pytest.mark.parametrize("d,f", [(64, 64), (128, 192), (192, 320), (256, 448), (320, 576), (704, 128)])
+@pytest.mark.parametrize("load", sorted(LOADS))
+def test_rows_against_the_oracle(load, d, f, cls):
+    _against_the_oracle(LOADS[load], d, f, cls, load)
+
+
+@pytest.mark.parametrize("d,f", TALL_WIDTHS)
+def test_tall_tiles_against_the_oracle(d, f):
+    _against_the_oracle(TALL_ROWS, d, f, 1, "tall")

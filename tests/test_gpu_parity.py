@@ -213,13 +213,12 @@ FFN_CASES = [
     ("rows32_class", 4, 192, 320, 1300, 3),
     ("rows256_class", 3, 256, 320, 2000, 4),
     ("rows256_ragged", 5, 192, 128, 1463, 4),
-    ("many_tiles_per_expert", 2, 128, 192, 5000, 1),   # > 8 row tiles per expert: several pieces per weight tile
-    # work-list layouts: pieces of unequal length (odd piece counts), many experts with few tiles each
-    # over several weight-row tiles, single-tile pieces
-    ("sched_uneven_pieces", 3, 64, 1024, 12000, 1),
-    ("sched_uneven_pieces_256", 3, 64, 1024, 12000, 4),
+    ("many_tiles_per_expert", 2, 128, 192, 5000, 1),   # > 8 row tiles per expert: several row ranges
+    # work lists: row ranges of unequal length over several weight-row tiles, many experts with few tiles each
+    ("sched_uneven_ranges", 3, 64, 1024, 12000, 1),
+    ("sched_uneven_ranges_256", 3, 64, 1024, 12000, 4),
     ("sched_many_experts", 40, 64, 640, 9000, 1),
-    ("sched_single_tile_pieces", 3, 64, 384, 12000, 1),
+    ("sched_three_weight_tiles", 3, 64, 384, 12000, 1),
     # few work items and a long reduction: the second GEMM runs as 2 (f = 2048) or 4 (f = 4096) reduction
     # splits with fp32 partial sums
     ("gemm2_two_splits", 4, 128, 2048, 100, -1),

@@ -1,13 +1,10 @@
 """Work of the eight XCDs in a work list (csrc/moe_schedule.h, compiled for the host) of row tiles of unequal height: nothing
 is stolen between their queues, so the tall tiles must not gather in one of them."""
 import os
-import shutil
-import subprocess
 
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+import sched_host
 
 PROGRAM = r"""
 #include "moe_schedule.h"
@@ -43,24 +40,17 @@ CASES = {
 
 @pytest.fixture(scope="module")
 def program(tmp_path_factory):
-    if not os.path.exists(HIPCC):
+    if not os.path.exists(sched_host.HIPCC):
         pytest.skip("no hipcc")
-    d = tmp_path_factory.mktemp("balance")
-    (d / "balance.hip").write_text(PROGRAM)
-    csrc = os.path.join(ROOT, "paper_2605_19945_amd", "csrc")
-    r = subprocess.run([HIPCC, "-O1", "-std=c++17", "--offload-arch=gfx950", "-I", csrc, "-o", str(d / "balance"),
-                        str(d / "balance.hip")], capture_output=True, text=True)
-    assert r.returncode == 0, r.stderr[-2000:]
-    return str(d / "balance")
+    return sched_host.compile_host(PROGRAM, str(tmp_path_factory.mktemp("balance")))
 
 
 @pytest.mark.parametrize("case", sorted(CASES))
 def test_unequal_heights_are_spread_over_the_xcds(program, case):
     experts, nt = CASES[case]
     heights = [h for tiles, h in experts for _ in range(tiles * nt)]
-    r = subprocess.run([program], input=f"{len(heights)} " + " ".join(map(str, heights)), capture_output=True, text=True)
-    assert r.returncode == 0
-    work = [int(v) for v in r.stdout.split()]
+    out = sched_host.run(program, f"{len(heights)} " + " ".join(map(str, heights)))
+    work = [int(v) for v in out.split()]
     assert sum(work) == sum(h + 1 for h in heights)
     # Heights that only rise or only fall: in a pair of laps an XCD has chunks x and 15 - x, so two XCDs differ by no more
     # than one chunk times the drop in those laps; the drops of all laps and of the stretch behind them add up to the whole

@@ -1,14 +1,13 @@
 """The order of a work list (csrc/moe_schedule.h, compiled for the host): for every number of heavy and light tiles up to 300,
 and around the numbers at which the heavy ones are dealt in longer chunks, each tile stands in exactly one entry, no queue
-holds more than an eighth of them rounded up, and nothing stands behind the entries that every launch has."""
+holds more than an eighth of them rounded up, and nothing stands behind the entries that every launch has; in whole lists
+of random loads every 32-row block of every expert meets every weight-row tile once."""
 import os
-import shutil
-import subprocess
 
+import numpy as np
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+import sched_host
 
 PROGRAM = r"""
 #include "moe_schedule.h"
@@ -46,13 +45,49 @@ int main() {
 """
 
 
-@pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
+needs_hipcc = pytest.mark.skipif(not os.path.exists(sched_host.HIPCC), reason="no hipcc")
+
+
+@needs_hipcc
 def test_every_tile_stands_in_one_entry(tmp_path):
-    src, exe = tmp_path / "entries.hip", tmp_path / "entries"
-    src.write_text(PROGRAM)
-    csrc = os.path.join(ROOT, "paper_2605_19945_amd", "csrc")
-    r = subprocess.run([HIPCC, "-O1", "-std=c++17", "--offload-arch=gfx950", "-I", csrc, "-o", str(exe), str(src)],
-                       capture_output=True, text=True)
-    assert r.returncode == 0, r.stderr[-2000:]
-    r = subprocess.run([str(exe)], capture_output=True, text=True)
-    assert r.returncode == 0, r.stdout
+    sched_host.run(sched_host.compile_host(PROGRAM, str(tmp_path)), "")
+
+
+@pytest.fixture(scope="module")
+def lists(tmp_path_factory):
+    return sched_host.compile_host(sched_host.PROGRAM, str(tmp_path_factory.mktemp("lists")))
+
+
+def _loads(kind, E, rng):
+    if kind == "zipf":
+        return [int(20000 / (e + 1)) for e in rng.permutation(E)]
+    if kind == "sparse":
+        return [int(n) for n in rng.integers(0, 2, E) * rng.integers(1, 700, E)]
+    if kind == "one_block":
+        return [int(n) for n in rng.integers(0, 33, E)]
+    return [int(n) for n in rng.integers(0, 1200, E)]
+
+
+@needs_hipcc
+@pytest.mark.parametrize("kind", ["zipf", "sparse", "one_block", "even"])
+@pytest.mark.parametrize("E,nt,bm", [(1, 1, 288), (3, 112, 288), (8, 16, 128), (31, 5, 64), (64, 24, 288), (256, 7, 288)])
+def test_every_block_of_rows_meets_every_weight_row_tile_once(lists, kind, E, nt, bm):
+    rows = _loads(kind, E, np.random.default_rng(E * nt + len(kind)))
+    cap, entries = sched_host.work_list(lists, rows, nt, bm)
+    off = np.concatenate([[0], np.cumsum(rows)])
+    seen = set()
+    for e, row0, n, n0, _ in entries:
+        assert 0 < n <= 32 * cap and (row0 - off[e]) % 32 == 0 and off[e] <= row0 and row0 + n <= off[e + 1]
+        assert n % 32 == 0 or row0 + n == off[e + 1]
+        for r in range(row0, row0 + n, 32):
+            assert (r, n0) not in seen
+            seen.add((r, n0))
+    assert len(seen) == nt * sum((n + 31) // 32 for n in rows) and {n0 for _, n0 in seen} <= {256 * i for i in range(nt)}
+
+
+@needs_hipcc
+def test_the_tall_loads_of_the_gpu_tests_keep_their_tiles(lists):
+    from test_gpu_group_loads import TALL_ROWS, TALL_WIDTHS
+    for nt in {(2 * f + 255) // 256 for _, f in TALL_WIDTHS} | {(d + 255) // 256 for d, _ in TALL_WIDTHS}:
+        _, entries = sched_host.work_list(lists, TALL_ROWS, nt)
+        assert {(rows + 31) // 32 for _, _, rows, _, _ in entries} == {5, 6, 7, 8, 9}, nt
