@@ -23,10 +23,11 @@
  *     nothing.  MOE_ERR_DEVICE reports a HIP call that failed part-way; in a call of several stages
  *     (moe_permute, moe_grouped_ffn, moe_layer_forward) the stages enqueued before it still run, and the
  *     outputs are then undefined.  T == 0 is MOE_OK and a no-op.
- *   - Calls on one moe_ctx must not overlap in time (they share its workspace).
+ *   - Calls on one moe_ctx must not overlap in time (they share its workspace).  Counters of the router live in it
+ *     from call to call: after calls that did overlap, later ones may count wrongly until the context is created anew.
  *   - The calls that take a stream only launch kernels on it (no memsets, no allocation, no host
  *     synchronisation), so they may be recorded under stream capture and replayed as a HIP graph; the
- *     exceptions are contexts created with MOE_FLAG_STAGE_EVENTS (they record events), moe_profile_ffn
+ *     exceptions are contexts created with MOE_FLAG_STAGE_EVENTS (they record events), moe_profile_ffn,
  *     moe_measure_mfma_rate(_of) and moe_measure_hbm_read_rate (they time and wait).
  */
 #ifndef MOE_H_
@@ -250,9 +251,11 @@ moe_status moe_gem_place(const int32_t* trace, int32_t S, int32_t E, int32_t G, 
 
 /* Tuning hook: force the token-tile class of the expert GEMMs (1: row tiles of up to 288 rows, the main
  * class; 5: the class of decode-sized loads -- two wavefronts per workgroup, 128 weight rows and up to 64
- * token rows per work item, four workgroups to a compute unit; 0, 2, 3, 4: alternative kernels with row tiles
- * of up to 128, 64, 32, 256 rows kept for tuning runs; -1: choose from the expected rows per expert, the
- * default: class 0 below 12 rows per expert, class 5 up to 24, class 1 above). */
+ * token rows per work item, four workgroups to a compute unit; 0: up to 128 rows; 2, 3, 4: row tiles of up to
+ * 64, 32, 256 rows, kept for tuning runs (4 on the kernel of class 1); -1: choose from the expected rows per
+ * expert and the work items of the launches, the default: class 0 below 12 rows per expert, class 5 up to 24,
+ * class 1 above; up to 4 rows class 5 where the first GEMM has few work items; from 12 to 24 rows class 0 or 1
+ * where both GEMMs fill the device). */
 moe_status moe_set_tile_class(moe_ctx* ctx, int32_t tile_class);
 
 /* Measurement aid for roofline reports: the bf16 matrix-core rate this device SUSTAINS under a load of

@@ -1,7 +1,7 @@
 """ctypes binding of include/moe.h.  Argument marshalling only.
 
 PyTorch is used for device memory and streams: tensors are passed as raw device pointers
-(`data_ptr()`), the stream as `torch.cuda.current_stream().cuda_stream`.
+(`data_ptr()`), the stream as the raw handle of the current one.
 """
 from __future__ import annotations
 

@@ -186,8 +186,8 @@ moe_status moe_create(moe_ctx** out, const moe_shape* s, void* workspace, size_t
     c->last_cls = -1;
     c->forced_cls = -1;
     c->table_r_T = -1;
-    // the resident router's ticket counter must be zero before the first launch (each launch leaves
-    // it at zero again); synchronous, creation is not on the hot path
+    // the routers' ticket and sub-counters must be zero before the first launch (each launch leaves
+    // them at zero again); synchronous, creation is not on the hot path
     if (note_hip(hipMemset(c->route_ws, 0, (size_t)MOE_ROUTE_WS_INTS * 4), "hipMemset(workspace)") != MOE_OK) {
         delete c;
         return MOE_ERR_DEVICE;

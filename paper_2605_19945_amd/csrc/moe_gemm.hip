@@ -18,7 +18,7 @@ __global__ __launch_bounds__(256) void schedule_kernel(const int32_t* __restrict
 // ------------------------------------------------------------------------------------------------
 // Host side: tile classes, plans, launches.  Class ids index the variants listed in
 // moe_gemm_kernel.h: 0 = 128-row tiles (very low loads), 1 = 288-row tiles (main), 2 = 64, 3 = 32,
-// 4 = 256.
+// 4 = 256, 5 = 64 by 128 weight rows (decode-sized loads).
 // ------------------------------------------------------------------------------------------------
 static const int kClassRows[GEMM_NUM_CLASSES] = {128, 288, 64, 32, 256, 64};
 static const int kClassBn[GEMM_NUM_CLASSES] = {256, 256, 256, 256, 256, 128};   // packed weight rows per work item
@@ -87,7 +87,7 @@ static bool gemm_fills_rounds(int items) {
     return 2 * items >= 3 * SCHED_CU && 5 * items >= 4 * rounds * SCHED_CU;
 }
 
-int gemm_pick_class_for(double n_assigned, int E_seen, int E_local, int d, int f) {
+extern "C" int gemm_pick_class_for(double n_assigned, int E_seen, int E_local, int d, int f) {
     const double mean = n_assigned / E_seen;
     const int cls = gemm_pick_class(mean);
     const int nt1 = (2 * f + GEMM_BN - 1) / GEMM_BN, nt2 = (d + GEMM_BN - 1) / GEMM_BN;

@@ -39,6 +39,8 @@
 //     and the epilogue between nine K loops keeps registers alive through all of them.  The last K steps
 //     test once per sub-step whether they still request anything, not once per load; together with the scalar base
 //     of the token loads this also compiles in a sixth of the time.
+//     The 288-row kernel still spills 13 registers (second GEMM) and 15 (first), outside all loops: around the code of
+//     the 8- and 9-block tiles, seven or eight stores and loads of a lane for a tile.
 //   * one wavefront per SIMD (256 threads, up to 512 registers per lane, accumulators in AGPRs),
 //     so all latency hiding is explicit: LDS fragment reads run one MFMA sub-step ahead, the
 //     barrier that publishes stage kt+1 sits before the LAST sub-step of stage kt so that the first
@@ -332,7 +334,6 @@ static __device__ __forceinline__ void gemm_tile(int bx, const uint16_t* __restr
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lrow = lane / CH, lphys = lane % CH;
-    const int frow = lane & 15, fq = lane >> 4;
     const int KT = K / BK;
     const int fmv = (td.rows + 31) / 32;  // valid 32-row blocks: the same for all four wavefronts
     const int K_total = K * (int)gridDim.y;
@@ -588,8 +589,8 @@ static __device__ __forceinline__ void gemm_tile(int bx, const uint16_t* __restr
 // unit has in flight: a 4-wavefront workgroup with all its registers keeps 64 KB of weights under way and
 // occupies the compute unit alone; these workgroups need under 256 registers per lane and 24 KB of LDS, four
 // of them share a compute unit, together they keep 128 KB under way, and the weight panels are half as large,
-// so a launch has four times as many workgroups to spread over the device (Mixtral shape, 64 tokens: 1792
-// instead of 896 for 256 compute units).
+// so a launch has twice as many workgroups for the device to place, four to a compute unit (Mixtral shape, 64
+// tokens: 1792 instead of 896).
 // A unit that defines MOE_GEMM_NO_TALL_TILE before including this file leaves out the 288-row class (its
 // launcher then rejects class 1): the router-logit GEMM never uses it, and with that unit's epilogue the
 // compiler copies the VGPR accumulators right behind their MFMAs (see mfma_pinned_vgpr).

@@ -78,7 +78,7 @@ struct moe_ctx {
     TileDesc* table_r;   // router GEMM work list (E >= MOE_ROUTER_GEMM_MIN_E)
     int table_r_T;       // token count table_r was built for; -1: none yet; -2: rebuild at every call
     float* logits;       // [T_max, router cols] fp32 (E >= MOE_ROUTER_GEMM_MIN_E)
-    int32_t* route_ws;   // [MOE_ROUTE_WS_INTS] resident router: ticket (zero between launches) + partial counts
+    int32_t* route_ws;   // [MOE_ROUTE_WS_INTS] ticket, partial and sub-counters of the routers (see MOE_ROUTE_WS_SUBCOUNTS)
     int32_t* refused;    // [1] 1 if the most recent work list was refused: offsets[E_local] exceeded the host's row bound
     uint16_t* H;         // [rows_cap, f] bf16
     uint16_t* Y;         // [rows_cap, d] bf16
@@ -110,8 +110,10 @@ static __host__ __device__ inline int moe_ld_pad(int K) { return K + 64; }
 constexpr int MOE_ROUTER_GEMM_MIN_E = 32;
 // Routers this small keep their matrix in registers (persistent kernel, see moe_route.hip).
 static inline bool moe_router_resident(int E, int d) { return E <= 8 && d % 512 == 0 && d <= 4096; }
-// Router scratch (ints, all zero between launches): ticket + per-workgroup partial counts of the
-// resident router, then 32 sub-counters per expert of the top-k kernel (GEMM path).
+// Router scratch (ints).  First the ticket of the workgroups that have counted, of the resident and the direct router;
+// then the per-workgroup partial counts of the resident one, overwritten by every launch; then 32 sub-counters per
+// expert, of the direct router and of the top-k kernel (GEMM path).  Ticket and sub-counters are zero between launches:
+// every launch relies on it and leaves them so, which holds as long as calls on a context do not overlap.
 constexpr int MOE_ROUTE_WS_SUBCOUNTS = 1 + 256 * 8 + 63;
 constexpr int MOE_ROUTE_WS_INTS = MOE_ROUTE_WS_SUBCOUNTS + 32 * 256;
 static inline int moe_router_cols(int E) { return (E + 31) / 32 * 32; }       // logits row length (GEMM path)
@@ -142,7 +144,7 @@ hipError_t launch_combine(const uint16_t* y, const int32_t* row_of, const float*
 
 GemmPlan gemm_make_plan(int cls, int64_t n_rows_cap, int E_local, int d, int f);
 int gemm_pick_class(double expected_rows_per_expert);
-int gemm_pick_class_for(double n_assigned, int E_seen, int E_local, int d, int f);
+extern "C" int gemm_pick_class_for(double n_assigned, int E_seen, int E_local, int d, int f);  // (C: called by its test)
 int gemm_class_rows(int cls);
 bool gemm_pick_stream(int cls, double expected_rows_per_expert);
 hipError_t gemm_init_attributes();

@@ -490,13 +490,9 @@ hipError_t launch_route(const uint16_t* x, const uint16_t* rp, const float* bias
         if (counts != nullptr) hipLaunchKernelGGL(reduce_counts_kernel, dim3(1), dim3(256), 0, st, sub, E, counts);
         return hipGetLastError();
     }
-    int nb = moe_router_rows(E) / 16;
-    switch (nb) {
+    switch (moe_router_rows(E) / 16) {
         case 1: return route_launch_t<1, 16>(x, rp, bias, T, d, E, k, idx, w, counts, route_ws, st);
         case 2: return route_launch_t<2, 8>(x, rp, bias, T, d, E, k, idx, w, counts, route_ws, st);
-        case 4: return route_launch_t<4, 4>(x, rp, bias, T, d, E, k, idx, w, counts, route_ws, st);
-        case 8: return route_launch_t<8, 4>(x, rp, bias, T, d, E, k, idx, w, counts, route_ws, st);
-        case 16: return route_launch_t<16, 2>(x, rp, bias, T, d, E, k, idx, w, counts, route_ws, st);
-        default: return hipErrorInvalidValue;
+        default: return hipErrorInvalidValue;  // more experts take the GEMM path above
     }
 }

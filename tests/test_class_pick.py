@@ -24,6 +24,6 @@ LOW, MAIN, DECODE = 0, 1, 5
 ])
 def test_class_at_the_lines(assigned, E, E_local, d, f, cls):
     import paper_2605_19945_amd as moe
-    pick = moe.load_library()._Z19gemm_pick_class_fordiiii
+    pick = moe.load_library().gemm_pick_class_for
     pick.restype, pick.argtypes = C.c_int, [C.c_double] + [C.c_int] * 4
     assert pick(assigned, E, E_local, d, f) == cls
