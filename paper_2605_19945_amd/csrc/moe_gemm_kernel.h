@@ -215,16 +215,46 @@ static __device__ inline void gemm_epilogue_staged(const f32x4_t (&acc_)[FA][Acc
             }
         }
     }
-    // the wavefront reads back only what it wrote itself
+    // The wavefront reads back only what it wrote itself, GRP wave-level stores at a time: the next group's LDS reads are
+    // under way while this group is stored.  What bounds the way out is that a compute unit takes a 1 KB store in no
+    // less than about 180 cycles, L2 hit or not (64 medium experts, 8192 tokens, GEMM2: without any stores 1119 us
+    // instead of 1256, with all of them into 32 rows for each XCD 1218), so nothing else may stand in line: read, wait and
+    // store one after the other cost a round trip to LDS for each of 36 (layer, us, that -> this: 64 medium experts
+    // 3862 -> 3845, 128 small experts, 8192 tokens, 671 -> 666, Mixtral shape, 4096 tokens, 2111 -> 2104).
     const int prow = td.n0 + wn * TN;  // first packed weight row of this wavefront
     if (prow >= Np) return;            // Np is a multiple of 64
     constexpr int RPI = 64 / NCH;      // rows per wave-level store
-    const int ch = lane % NCH;
-    uint16_t* cbase = C + (size_t)td.row0 * ldc + (EPI == EPI_SWIGLU ? prow / 2 : prow) + ch * 8;
-    for (int r = lane / NCH; r < td.rows; r += RPI) {
-        const u32x4_t v = *(const u32x4_t*)(stage + r * ROWB + ((ch ^ swz(r)) << 4));
-        *(u32x4_t*)(cbase + (size_t)r * ldc) = v;
-    }
+    constexpr int NIT = FT * 16 / RPI, GRP = EPI == EPI_SWIGLU ? 2 : 4, NG = NIT / GRP;
+    static_assert(NIT % GRP == 0, "whole groups");
+    const int ch = lane % NCH, r0 = lane / NCH;
+    char* const cbase = (char*)(C + (size_t)td.row0 * ldc + (EPI == EPI_SWIGLU ? prow / 2 : prow));  // wave-uniform
+    const uint32_t voff = (uint32_t)r0 * (uint32_t)(ldc * 2) + (uint32_t)ch * 16u;
+    const int lane_off = r0 * ROWB + ((ch ^ (EPI == EPI_SWIGLU ? (r0 >> 2) & 3 : r0)) << 4);
+    auto copy_out = [&](auto full_c) {
+        constexpr bool FULL = decltype(full_c)::value;  // every row of the tile exists
+        u32x4_t v[2][GRP];
+        auto fetch = [&](int g, u32x4_t (&dst)[GRP]) {
+#pragma unroll
+            for (int i = 0; i < GRP; ++i) {
+                const int it = g * GRP + i;  // rows it * RPI + r0; swz() of them as a fixed part and one of the place
+                const int off = EPI == EPI_SWIGLU ? lane_off : lane_off ^ ((it & 7) << 4);
+                dst[i] = *(const u32x4_t*)(stage + it * (RPI * ROWB) + off);
+            }
+        };
+        fetch(0, v[0]);
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            if (g + 1 < NG) fetch(g + 1, v[(g + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < GRP; ++i) {
+                const int r = (g * GRP + i) * RPI;
+                if (FULL || r + r0 < td.rows) *(u32x4_t*)(cbase + (size_t)r * (size_t)(ldc * 2) + voff) = v[g & 1][i];
+            }
+        }
+    };
+    if (td.rows == FT * 16) copy_out(std::true_type{});
+    else copy_out(std::false_type{});
 }
 
 template <int CH>
