@@ -163,6 +163,11 @@ static __device__ inline void gemm_epilogue(const f32x4_t (&acc_)[FA][AccShape<F
     }
 }
 
+// a 16-byte store that goes through the L2 instead of staying in it as a changed line; wave-uniform base
+static __device__ inline void store_through(char* base, uint32_t off, const u32x4_t& v) {
+    asm volatile("global_store_dwordx4 %0, %1, %2 sc1" ::"v"(off), "v"(v), "s"(base) : "memory");
+}
+
 // bf16 epilogues (EPI_PLAIN, EPI_SWIGLU) through LDS.  Stored straight from the accumulators, a wave-level
 // store would write 16 bytes to each of 32 rows; instead every wavefront parks its 64 output columns (32 after SwiGLU) of all rows in its own quarter of
 // the token ring, which nobody reads any more, and writes them back out row-contiguously: 16 bytes per
@@ -172,7 +177,7 @@ static __device__ inline void gemm_epilogue(const f32x4_t (&acc_)[FA][AccShape<F
 // tile) to 1.8 % (f = 768: 12 K steps per tile) of the layer time; most of the cost of the scattered
 // stores was their completion, which the wavefronts never waited for.
 // The caller has made sure that no wavefront still reads the ring.
-template <int FT, int FA, int BM, int TN, int EPI, bool NINE>
+template <int FT, int FA, int BM, int TN, int EPI, bool NINE, bool THROUGH>
 static __device__ inline void gemm_epilogue_staged(const f32x4_t (&acc_)[FA][AccShape<FT>::NA],
                                                    const f32x4_t (&accv_)[FA][AccShape<FT>::NV], const TileDesc& td,
                                                    int Np, uint16_t* __restrict__ C, int ldc, int wn, int lane,
@@ -249,7 +254,13 @@ static __device__ inline void gemm_epilogue_staged(const f32x4_t (&acc_)[FA][Acc
 #pragma unroll
             for (int i = 0; i < GRP; ++i) {
                 const int r = (g * GRP + i) * RPI;
-                if (FULL || r + r0 < td.rows) *(u32x4_t*)(cbase + (size_t)r * (size_t)(ldc * 2) + voff) = v[g & 1][i];
+                if (FULL || r + r0 < td.rows) {
+                    char* const row = cbase + (size_t)r * (size_t)(ldc * 2);
+                    if constexpr (THROUGH)
+                        store_through(row, voff, v[g & 1][i]);
+                    else
+                        *(u32x4_t*)(row + voff) = v[g & 1][i];
+                }
             }
         }
     };
@@ -599,7 +610,13 @@ static __device__ __forceinline__ void gemm_tile(int bx, const uint16_t* __restr
             static_assert(SMEM >= NW * BM * TN * 2, "staged output");
             // every wavefront has issued and completed its last reads of the token ring
             asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            gemm_epilogue_staged<FT, FA, BM, TN, EPI, FMV == 9>(acc, accv, td, Np, C, ldc, wave, elane, (char*)lds);
+            // Tall tiles of a streaming launch store through the L2: what is kept there as changed lines has to be written
+            // back before the streamed weights and the shared token rows can have its place.  Layer, us, kept -> through:
+            // expert-parallel share, 2048 tokens, 420 -> 402, 16 wide experts, 3001 tokens, 978 -> 946, Mixtral shape, skewed,
+            // 1000 tokens, 764 -> 754, 5003 Zipf-distributed rows 640 -> 627.  The launches with less output for
+            // each weight are 0.2 to 0.7 % slower with it (128-row class, 77 tokens, 187.2 against 188.6; decode class 438.3
+            // against 439.2), and those that share their weight panels gain nothing.
+            gemm_epilogue_staged<FT, FA, BM, TN, EPI, FMV == 9, W_STREAM && (BM > 128)>(acc, accv, td, Np, C, ldc, wave, elane, (char*)lds);
         } else {
             gemm_epilogue<FT, FA, TN, EPI, FMV == 9>(acc, accv, td, Np, C, ldc, wave, elane);
         }
