@@ -163,9 +163,11 @@ static __device__ inline void gemm_epilogue(const f32x4_t (&acc_)[FA][AccShape<F
     }
 }
 
-// a 16-byte store that goes through the L2 instead of staying in it as a changed line; wave-uniform base
-static __device__ inline void store_through(char* base, uint32_t off, const u32x4_t& v) {
-    asm volatile("global_store_dwordx4 %0, %1, %2 sc1" ::"v"(off), "v"(v), "s"(base) : "memory");
+// A 16-byte store of device scope (sc1).  The compiler's builtin, not inline asm: a vector instruction that overwrites the
+// data registers of a store of more than 64 bits has to stay two wait states behind it, which the compiler sees to for
+// the stores it knows (tests/test_isa_hazards.py allows no others).
+static __device__ inline void store_through(char* p, const u32x4_t& v) {
+    __builtin_amdgcn_global_store_b128((__attribute__((address_space(1))) u32x4_t*)p, v, "agent");
 }
 
 // bf16 epilogues (EPI_PLAIN, EPI_SWIGLU) through LDS.  Stored straight from the accumulators, a wave-level
@@ -257,7 +259,7 @@ static __device__ inline void gemm_epilogue_staged(const f32x4_t (&acc_)[FA][Acc
                 if (FULL || r + r0 < td.rows) {
                     char* const row = cbase + (size_t)r * (size_t)(ldc * 2);
                     if constexpr (THROUGH)
-                        store_through(row, voff, v[g & 1][i]);
+                        store_through(row + voff, v[g & 1][i]);
                     else
                         *(u32x4_t*)(row + voff) = v[g & 1][i];
                 }

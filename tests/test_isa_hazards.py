@@ -5,9 +5,12 @@ accumulator (AGPRs, and VGPRs for two token blocks of the 288-row tile), which t
 recogniser cannot see into.  Two things it would otherwise guarantee are checked here on the compiled code,
 instruction by instruction and following branches: nothing but the next accumulating MFMA touches an MFMA's
 result until it has been written (7 wait states after a 4-pass MFMA), and nothing writes an operand of an
-asm MFMA in the wait states right before it.
+asm MFMA in the wait states right before it.  Loads through inline asm are followed to the wait that covers them; stores
+through inline asm are not allowed at all.
 """
 import re
+
+import pytest
 
 NEED = 8           # wait states before anything else may touch the result (7 by the ISA tables, one to spare)
 MFMA_PASSES = 4    # v_mfma_f32_16x16x32_bf16; the pipe takes the next MFMA when the previous one has gone through
@@ -211,6 +214,40 @@ def find_touched_before_arrival(lines):
     return checked, crossed, bad
 
 
+def find_asm_stores(lines):
+    """Stores to memory issued through inline asm.  A vector instruction that overwrites the data registers of a store of
+    more than 64 bits needs two wait states behind it; the compiler inserts them for the stores it knows, not for these."""
+    bad, in_asm = [], False
+    for i, l in enumerate(lines):
+        s = l.strip()
+        if s.startswith(";;#ASM"):
+            in_asm = s.startswith(";;#ASMSTART")
+        elif in_asm and re.match(r"(global|flat|buffer|scratch)_store", s):
+            bad.append(f"line {i + 1}: store the compiler cannot see into: {s}")
+    return bad
+
+
+def test_lint_flags_an_asm_store():
+    st = "\tglobal_store_dwordx4 v64, v[40:43], s[22:23] sc1"
+    assert len(find_asm_stores(["\t;;#ASMSTART", st, "\t;;#ASMEND", "\tv_add_u32_e32 v40, 8, v1"])) == 1
+    assert find_asm_stores([st, "\t;;#ASMSTART", "\ts_nop 0", "\t;;#ASMEND", st]) == []
+
+
+@pytest.mark.parametrize("unit,heights", [("moe_gemm_plain_stream", {288}), ("moe_gemm_swiglu_stream", {288}),
+                                            ("moe_gemm_plain", set()), ("moe_gemm_swiglu", set())])
+def test_stores_of_device_scope_stand_in_the_tall_streaming_kernels_only(unit, heights, gemm_unit_asm):
+    kernel, scoped = None, set()
+    for line in gemm_unit_asm[unit]:
+        m = re.match(r"(_Z\w*grouped_gemm_kernelILi(\d+)E\w*):", line)
+        if m:
+            kernel = int(m.group(2))
+        op, ops = _split(line)
+        if op.startswith("global_store") and " sc1" in line:
+            assert op == "global_store_dwordx4"
+            scoped.add(kernel)
+    assert scoped == heights
+
+
 def test_lint_flags_a_register_used_before_its_load_arrived():
     ld = ["\t;;#ASMSTART", "\tglobal_load_dwordx4 v[10:13], v1, s[2:3] offset:0", "\t;;#ASMEND"]
     other = ["\t;;#ASMSTART", "\tglobal_load_dwordx4 v[20:23], v1, s[2:3] offset:1024", "\t;;#ASMEND"]
@@ -270,5 +307,7 @@ def test_no_hazard_around_the_mfmas_of_the_compiled_kernels(gemm_unit_asm):
         assert not bad, f"{unit}:\n" + "\n".join(bad[:10])
         n_asm, late = find_late_writers(lines)
         assert not late, f"{unit}:\n" + "\n".join(late[:10])
+        stores = find_asm_stores(lines)
+        assert not stores, f"{unit}: {len(stores)} stores\n" + "\n".join(stores[:10])
         n_loads, crossed, early = find_touched_before_arrival(lines)
         assert n_loads > 0 and crossed > 0 and not early, f"{unit}:\n" + "\n".join(early[:10])
