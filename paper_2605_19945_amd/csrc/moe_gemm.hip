@@ -29,7 +29,8 @@ constexpr int GEMM_BN = 256;  // of the classes the router-logit GEMM uses
     hipError_t gemm_set_attr_##name();                                                                     \
     hipError_t gemm_launch_##name(int cls, int grid, const uint16_t* X, int ldx, const int32_t* row_map,   \
                                   const uint16_t* Wf, int Np, int K, uint16_t* C, int ldc,                 \
-                                  const TileDesc* table, int nsplit, size_t c_split_bytes, hipStream_t st);
+                                  const TileDesc* table, int nsplit, size_t c_split_bytes, hipStream_t st, \
+                                  bool device_scope);
 DECL(swiglu) DECL(plain) DECL(pairsum) DECL(partial)
 DECL(swiglu_stream) DECL(plain_stream) DECL(partial_stream)  // weight loads with the non-temporal hint
 #undef DECL
@@ -42,7 +43,36 @@ int gemm_class_rows(int cls) { return kClassRows[cls]; }
 // class) 0.539 against 0.590, 1024 rows per expert 2.38 against 2.31; expert-parallel share, 4 rows per expert
 // (128-row class) 0.205 against 0.215, 530 rows per expert 1.40 against 1.41; fine-grained experts with 512
 // rows on average and up to 1500, 0.859 against 0.826.
-bool gemm_pick_stream(int cls, double rows_per_expert) { return rows_per_expert <= (double)kClassRows[cls]; }
+static bool gemm_pick_stream(int cls, double rows_per_expert) { return rows_per_expert <= (double)kClassRows[cls]; }
+
+// Output stores of device scope (bit 0: GEMM1, bit 1: GEMM2).  In the tall class with streamed weights they are up to 9 %
+// faster where a launch is bound by streaming and up to 12 % slower where tiles are short and outputs large.  (Why has
+// not been shown; stores with the non-temporal hint behave much the same.)  From 2280 loads on 253 shapes from d = 256 and
+// f = 256 up -- even, drawn, biased and Zipf-distributed, 26 to 288 rows per expert -- expert GEMMs, us, plain -> device
+// scope in that GEMM:
+//  * GEMM1 gains 1.0 % on average (1.7 up to 180 rows) while the mean load is no more than an eighth of the reduction
+//    length d (a short K loop leaves the stores a larger share of the tile): d = 576, 48 rows 213 -> 203, 240 rows
+//    310 -> 318; d = 1024, 96 rows 182 -> 176, 272 rows 257 -> 261; Mixtral shape, 256 rows 686 -> 676; share of 32
+//    experts, 128 rows 490 -> 476.
+//  * GEMM2 gains 0.7 % there up to 180 rows, and loses as often as it gains elsewhere: the share, 128 rows 490 -> 475; 16
+//    wide experts, 128 rows 738 -> 738; 96 experts, d = 2048, f = 512, 240 rows 181 -> 186.
+// The rule takes 0.7 % off on average (device scope everywhere 0.3 %); 63 of the loads (699) are slower than with
+// plain stores by more than 1 %, 14 (386) by more than 2 %, which is what some loads differ by from run to run with one
+// and the same code.  Of another 720 loads, on another device, 19 (149) and four (71).  The other classes are 0.2 to 0.7 %
+// slower with it (128-row class, 77 tokens, 187.2 against 188.6; decode class 438.3 against 439.2), and launches that
+// share their weight panels gain nothing.
+extern "C" int gemm_pick_scopes(int cls, double rows_per_expert, int d) {
+    if (kClassRows[cls] <= 128 || !gemm_pick_stream(cls, rows_per_expert)) return 0;
+    if (8.0 * rows_per_expert > d) return 0;
+    return rows_per_expert <= 180.0 ? 3 : 1;
+}
+
+void gemm_pick_hints(GemmPlan* p, double rows_per_expert, int d) {
+    p->w_stream = gemm_pick_stream(p->cls, rows_per_expert);
+    const int scopes = gemm_pick_scopes(p->cls, rows_per_expert, d);
+    p->scope1 = scopes & 1;
+    p->scope2 = scopes & 2;
+}
 
 int gemm_pick_class(double rows_per_expert) {
     // Measured on the layer time of the Mixtral shape, near-uniform loads (ms; classes 5 / 0 / 1 = decode,
@@ -114,7 +144,7 @@ GemmPlan gemm_make_plan(int cls, int64_t n_rows_cap, int E_local, int d, int f) 
     p.nt2 = (d + p.bn - 1) / p.bn;
     p.grid1 = sched_grid(p.mt_max, p.nt1);
     p.grid2 = sched_grid(p.mt_max, p.nt2);
-    p.w_stream = false;  // the caller decides from the load it expects (gemm_pick_stream)
+    p.w_stream = p.scope1 = p.scope2 = false;  // the caller decides from the load it expects (gemm_pick_hints)
     return p;
 }
 
@@ -162,7 +192,7 @@ hipError_t launch_schedule(const GemmPlan& p, const int32_t* offsets, int E_loca
 hipError_t launch_gemm1(const GemmPlan& p, const uint16_t* X, int ldx, const int32_t* row_map,
                         const uint16_t* W13f, int d, int f, uint16_t* H, const TileDesc* table, hipStream_t st) {
     if (p.grid1 <= 0) return hipSuccess;
-    return (p.w_stream ? gemm_launch_swiglu_stream : gemm_launch_swiglu)(p.cls, p.grid1, X, ldx, row_map, W13f, 2 * f, d, H, moe_ld_pad(f), table, 1, 0, st);
+    return (p.w_stream ? gemm_launch_swiglu_stream : gemm_launch_swiglu)(p.cls, p.grid1, X, ldx, row_map, W13f, 2 * f, d, H, moe_ld_pad(f), table, 1, 0, st, p.scope1);
 }
 
 // Reduction splits of the second expert GEMM.  With few resident experts and few rows it has far fewer
@@ -244,10 +274,10 @@ hipError_t launch_gemm2(const GemmPlan& p, const uint16_t* H, const uint16_t* W2
                         hipStream_t st) {
     if (p.grid2 <= 0) return hipSuccess;
     if (nsplit <= 1)
-        return (p.w_stream ? gemm_launch_plain_stream : gemm_launch_plain)(p.cls, p.grid2, H, moe_ld_pad(f), nullptr, W2f, d, f, Y, d, table, 1, 0, st);
+        return (p.w_stream ? gemm_launch_plain_stream : gemm_launch_plain)(p.cls, p.grid2, H, moe_ld_pad(f), nullptr, W2f, d, f, Y, d, table, 1, 0, st, p.scope2);
     const size_t slab_elems = (size_t)n_rows * d;
     hipError_t e = (p.w_stream ? gemm_launch_partial_stream : gemm_launch_partial)(p.cls, p.grid2, H, moe_ld_pad(f), nullptr, W2f, d, f / nsplit, (uint16_t*)part, d,
-                                       table, nsplit, slab_elems * 4, st);
+                                       table, nsplit, slab_elems * 4, st, false);
     if (e != hipSuccess || Y == nullptr) return e;  // Y == nullptr: the caller consumes the partial slabs
     size_t blocks = (slab_elems / 4 + 255) / 256;
     if (blocks > 2048) blocks = 2048;
@@ -318,7 +348,7 @@ hipError_t launch_router_gemm(const uint16_t* x, const uint16_t* rp, int T, int 
         if (*table_T != -2) *table_T = T;
     }
     return gemm_launch_pairsum(c, grid, x, d, nullptr, rp, Rp, d / pk.nsplit, (uint16_t*)logits, ldl, table, pk.nsplit,
-                               (size_t)T * ldl * sizeof(float), st);
+                               (size_t)T * ldl * sizeof(float), st, false);
 }
 
 // ---- sustained matrix-core rate (measurement aid) ------------------------------------------------

@@ -166,7 +166,7 @@ static __device__ inline void gemm_epilogue(const f32x4_t (&acc_)[FA][AccShape<F
 // A 16-byte store of device scope (sc1).  The compiler's builtin, not inline asm: a vector instruction that overwrites the
 // data registers of a store of more than 64 bits has to stay two wait states behind it, which the compiler sees to for
 // the stores it knows (tests/test_isa_hazards.py allows no others).
-static __device__ inline void store_through(char* p, const u32x4_t& v) {
+static __device__ inline void store_device_scope(char* p, const u32x4_t& v) {
     __builtin_amdgcn_global_store_b128((__attribute__((address_space(1))) u32x4_t*)p, v, "agent");
 }
 
@@ -179,11 +179,11 @@ static __device__ inline void store_through(char* p, const u32x4_t& v) {
 // tile) to 1.8 % (f = 768: 12 K steps per tile) of the layer time; most of the cost of the scattered
 // stores was their completion, which the wavefronts never waited for.
 // The caller has made sure that no wavefront still reads the ring.
-template <int FT, int FA, int BM, int TN, int EPI, bool NINE, bool THROUGH>
+template <int FT, int FA, int BM, int TN, int EPI, bool NINE, bool MAY_SCOPE>
 static __device__ inline void gemm_epilogue_staged(const f32x4_t (&acc_)[FA][AccShape<FT>::NA],
                                                    const f32x4_t (&accv_)[FA][AccShape<FT>::NV], const TileDesc& td,
                                                    int Np, uint16_t* __restrict__ C, int ldc, int wn, int lane,
-                                                   char* lds_base) {
+                                                   char* lds_base, bool device_scope) {
     auto A = [&](int a, int t) -> const f32x4_t& {
         return acc_at<NINE, FA, AccShape<FT>::NA, AccShape<FT>::NV>(acc_, accv_, a, t);
     };
@@ -237,7 +237,7 @@ static __device__ inline void gemm_epilogue_staged(const f32x4_t (&acc_)[FA][Acc
     char* const cbase = (char*)(C + (size_t)td.row0 * ldc + (EPI == EPI_SWIGLU ? prow / 2 : prow));  // wave-uniform
     const uint32_t voff = (uint32_t)r0 * (uint32_t)(ldc * 2) + (uint32_t)ch * 16u;
     const int lane_off = r0 * ROWB + ((ch ^ (EPI == EPI_SWIGLU ? (r0 >> 2) & 3 : r0)) << 4);
-    auto copy_out = [&](auto full_c) {
+    auto copy_out = [&](auto full_c, auto scope_c) {
         constexpr bool FULL = decltype(full_c)::value;  // every row of the tile exists
         u32x4_t v[2][GRP];
         auto fetch = [&](int g, u32x4_t (&dst)[GRP]) {
@@ -258,16 +258,24 @@ static __device__ inline void gemm_epilogue_staged(const f32x4_t (&acc_)[FA][Acc
                 const int r = (g * GRP + i) * RPI;
                 if (FULL || r + r0 < td.rows) {
                     char* const row = cbase + (size_t)r * (size_t)(ldc * 2);
-                    if constexpr (THROUGH)
-                        store_through(row + voff, v[g & 1][i]);
+                    if constexpr (decltype(scope_c)::value)
+                        store_device_scope(row + voff, v[g & 1][i]);
                     else
                         *(u32x4_t*)(row + voff) = v[g & 1][i];
                 }
             }
         }
     };
-    if (td.rows == FT * 16) copy_out(std::true_type{});
-    else copy_out(std::false_type{});
+    const bool full = td.rows == FT * 16;
+    if constexpr (MAY_SCOPE) {
+        if (device_scope) {
+            if (full) copy_out(std::true_type{}, std::true_type{});
+            else copy_out(std::false_type{}, std::true_type{});
+            return;
+        }
+    }
+    if (full) copy_out(std::true_type{}, std::false_type{});
+    else copy_out(std::false_type{}, std::false_type{});
 }
 
 template <int CH>
@@ -354,7 +362,8 @@ static __device__ __forceinline__ void gemm_tile(int bx, const uint16_t* __restr
                                                  const int32_t* __restrict__ row_map,
                                                  const uint16_t* __restrict__ Wf, int Np, int K,
                                                  uint16_t* __restrict__ C, int ldc,
-                                                 const TileDesc* __restrict__ table, size_t c_split_bytes) {
+                                                 const TileDesc* __restrict__ table, size_t c_split_bytes,
+                                                 bool device_scope) {
     constexpr int BN = 64 * NW, BK = 64, TN = BN / NW, FA = TN / 16, FM = BM / 32;
     constexpr int CH = BK / 8;   // 16-byte chunks per staged token row
     constexpr int RPL = 64 / CH; // rows covered by one wave-level load
@@ -612,13 +621,8 @@ static __device__ __forceinline__ void gemm_tile(int bx, const uint16_t* __restr
             static_assert(SMEM >= NW * BM * TN * 2, "staged output");
             // every wavefront has issued and completed its last reads of the token ring
             asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            // Tall tiles of a streaming launch store through the L2: what is kept there as changed lines has to be written
-            // back before the streamed weights and the shared token rows can have its place.  Layer, us, kept -> through:
-            // expert-parallel share, 2048 tokens, 420 -> 402, 16 wide experts, 3001 tokens, 978 -> 946, Mixtral shape, skewed,
-            // 1000 tokens, 764 -> 754, 5003 Zipf-distributed rows 640 -> 627.  The launches with less output for
-            // each weight are 0.2 to 0.7 % slower with it (128-row class, 77 tokens, 187.2 against 188.6; decode class 438.3
-            // against 439.2), and those that share their weight panels gain nothing.
-            gemm_epilogue_staged<FT, FA, BM, TN, EPI, FMV == 9, W_STREAM && (BM > 128)>(acc, accv, td, Np, C, ldc, wave, elane, (char*)lds);
+            // (only the tall streaming kernels are compiled with stores of device scope: gemm_pick_hints)
+            gemm_epilogue_staged<FT, FA, BM, TN, EPI, FMV == 9, W_STREAM && (BM > 128)>(acc, accv, td, Np, C, ldc, wave, elane, (char*)lds, device_scope);
         } else {
             gemm_epilogue<FT, FA, TN, EPI, FMV == 9>(acc, accv, td, Np, C, ldc, wave, elane);
         }
@@ -684,10 +688,10 @@ __global__ __launch_bounds__(NW * 64) void grouped_gemm_kernel(const uint16_t* _
                                                                const uint16_t* __restrict__ Wf, int Np, int K,
                                                                uint16_t* __restrict__ C, int ldc,
                                                                const TileDesc* __restrict__ table,
-                                                               size_t c_split_bytes, int n_entries) {
+                                                               size_t c_split_bytes, int n_entries, bool device_scope) {
     if constexpr (NW == 2) {
         for (int b = blockIdx.x; b < n_entries; b += gridDim.x) {
-            gemm_tile<BM, EPI, NW, W_STREAM>(b, X, ldx, row_map, Wf, Np, K, C, ldc, table, c_split_bytes);
+            gemm_tile<BM, EPI, NW, W_STREAM>(b, X, ldx, row_map, Wf, Np, K, C, ldc, table, c_split_bytes, device_scope);
             // LDS reads only: the output stores need not have completed (a full __syncthreads() would also
             // wait for them, and a workgroup that waits for its last stores holds its compute unit longer)
             if (b + (int)gridDim.x < n_entries) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -695,7 +699,7 @@ __global__ __launch_bounds__(NW * 64) void grouped_gemm_kernel(const uint16_t* _
     } else {
         // no loop in the code of the other classes: the compiler would keep the lane-dependent values it can
         // hoist out of it in registers for the whole kernel, and the tall tiles have none to spare
-        gemm_tile<BM, EPI, NW, W_STREAM>(blockIdx.x, X, ldx, row_map, Wf, Np, K, C, ldc, table, c_split_bytes);
+        gemm_tile<BM, EPI, NW, W_STREAM>(blockIdx.x, X, ldx, row_map, Wf, Np, K, C, ldc, table, c_split_bytes, device_scope);
     }
 }
 
@@ -709,11 +713,11 @@ struct Variant {
     // K is the reduction length of ONE split; nsplit = 1 for the expert GEMMs
     static hipError_t launch(int grid, const uint16_t* X, int ldx, const int32_t* row_map, const uint16_t* Wf,
                              int Np, int K, uint16_t* C, int ldc, const TileDesc* table, int nsplit,
-                             size_t c_split_bytes, hipStream_t st) {
+                             size_t c_split_bytes, hipStream_t st, bool device_scope) {
         constexpr int RESIDENT = 256 * 4;  // decode class: four workgroups fit a compute unit
         const int gx = (NW == 2 && grid > RESIDENT) ? RESIDENT : grid;
         hipLaunchKernelGGL((grouped_gemm_kernel<BM, EPI, NW, WS>), dim3(gx, nsplit), dim3(NW * 64), smem, st,
-                           X, ldx, row_map, Wf, Np, K, C, ldc, table, c_split_bytes, grid);
+                           X, ldx, row_map, Wf, Np, K, C, ldc, table, c_split_bytes, grid, device_scope);
         return hipGetLastError();
     }
 };
@@ -732,12 +736,12 @@ static hipError_t gemm_set_attr_all() {
 template <int EPI, bool WS>
 static hipError_t gemm_launch_any(int cls, int grid, const uint16_t* X, int ldx, const int32_t* row_map,
                                   const uint16_t* Wf, int Np, int K, uint16_t* C, int ldc, const TileDesc* table,
-                                  int nsplit, size_t c_split_bytes, hipStream_t st) {
+                                  int nsplit, size_t c_split_bytes, hipStream_t st, bool device_scope) {
     switch (variant_of_class(cls)) {
 #define V(id, bm, nw)                                                                                     \
     case id:                                                                                                  \
         return Variant<bm, EPI, nw, WS>::launch(grid, X, ldx, row_map, Wf, Np, K, C, ldc, table, nsplit,  \
-                                                    c_split_bytes, st);
+                                                    c_split_bytes, st, device_scope);
         FOR_EACH_VARIANT(V)
 #undef V
     }
@@ -750,7 +754,8 @@ static hipError_t gemm_launch_any(int cls, int grid, const uint16_t* X, int ldx,
     hipError_t gemm_set_attr_##name() { return gemm_set_attr_all<EPI, WS>(); }                                \
     hipError_t gemm_launch_##name(int cls, int grid, const uint16_t* X, int ldx, const int32_t* row_map,      \
                                   const uint16_t* Wf, int Np, int K, uint16_t* C, int ldc,                    \
-                                  const TileDesc* table, int nsplit, size_t c_split_bytes, hipStream_t st) {  \
+                                  const TileDesc* table, int nsplit, size_t c_split_bytes, hipStream_t st,    \
+                                   bool device_scope) {                                                       \
         return gemm_launch_any<EPI, WS>(cls, grid, X, ldx, row_map, Wf, Np, K, C, ldc, table, nsplit,         \
-                                        c_split_bytes, st);                                                   \
+                                        c_split_bytes, st, device_scope);                                     \
     }

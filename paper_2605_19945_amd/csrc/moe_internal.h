@@ -55,7 +55,8 @@ struct GemmPlan {
     int mt_max;      // upper bound on the number of row tiles
     int nt1, nt2;    // weight-row tiles of GEMM1 (2f packed rows) and GEMM2 (d rows)
     int grid1, grid2;
-    bool w_stream;   // weight loads carry the non-temporal hint (gemm_pick_stream)
+    bool w_stream;   // weight loads carry the non-temporal hint (gemm_pick_hints)
+    bool scope1, scope2;  // the tall tiles' output stores have device scope, in GEMM1 and GEMM2 (gemm_pick_hints)
 };
 
 constexpr int MOE_EVENT_RING = 64;
@@ -146,7 +147,8 @@ GemmPlan gemm_make_plan(int cls, int64_t n_rows_cap, int E_local, int d, int f);
 int gemm_pick_class(double expected_rows_per_expert);
 extern "C" int gemm_pick_class_for(double n_assigned, int E_seen, int E_local, int d, int f);  // (C: called by its test)
 int gemm_class_rows(int cls);
-bool gemm_pick_stream(int cls, double expected_rows_per_expert);
+extern "C" int gemm_pick_scopes(int cls, double rows_per_expert, int d);  // (C: called by its test)
+void gemm_pick_hints(GemmPlan* p, double expected_rows_per_expert, int d);
 hipError_t gemm_init_attributes();
 int router_gemm_grid_max(int T_max, int Rp);
 hipError_t launch_router_gemm(const uint16_t* x, const uint16_t* rp, int T, int d, int Rp, float* logits, int ldl,
