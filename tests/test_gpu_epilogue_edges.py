@@ -1,6 +1,8 @@
-"""Staged output of the expert GEMMs at the edges of its row groups: one expert of n rows, n around the multiples of 8, 16
-and 32 rows that leave together, of full and ragged tiles of every height, stored through the L2 (up to one tall tile) and
-not; rows behind the last one stay untouched."""
+"""Staged output of the expert GEMMs at the edges of its row groups, with rows behind the last one that have to stay
+untouched: one expert of n rows, n around the multiples of 8, 16 and 32 rows that leave together (few work items, so
+the device cuts it to tiles of one to four blocks of 32 rows in the tall class and of one block in the others), and 128
+experts that fill whole rounds with uncut tiles, the last of them, of every height, ragged or full, at the end of the
+buffer (test_schedule_entries.py holds the work lists to that)."""
 import numpy as np
 import pytest
 
@@ -31,4 +33,53 @@ def test_rows_at_the_edges_of_the_groups(cls, rows):
         torch.cuda.synchronize()
         gu.check_output(gu.f64_of_bf16(y[:n]), ref[:n], what=f"class {cls}, {n} rows")
         assert bool((y[n:] == 7.0).all()), f"rows past {n} were written"
+    ctx.close()
+
+
+# 128 experts, d = 1024, f = 256: 256 and 512 work items (class 5: 512 and 1024) if no expert is cut, which are whole rounds.
+# Loads by class and kind of stores: rows of all experts but the last, 32-row blocks of the last one.
+E, D, F = 128, 1024, 256
+TALL = [32 * (5 + e % 5) - (0, 1, 13, 31)[e // 5 % 4] for e in range(E - 1)]
+WHOLE_LOADS = {
+    (1, "plain"): (TALL, (5, 6, 7, 8, 9)),
+    (1, "device scope"): ([n if e % 2 else 1 + e % 32 for e, n in enumerate(TALL)], (5, 6, 7, 8, 9)),
+    (0, "plain"): ([32 * (2 + e % 3) - (0, 5, 31)[e // 3 % 3] for e in range(E - 1)], (2, 3, 4)),
+    (5, "plain"): ([64 - e % 40 for e in range(E - 1)], (1, 2)),
+}
+LAST = (0, 1, 13, 24, 31)  # rows missing from the last block
+
+
+@pytest.fixture(scope="module")
+def experts():
+    import torch
+    g = torch.Generator().manual_seed(3)
+    return [torch.empty(s, dtype=torch.bfloat16).normal_(0, a ** -0.5, generator=g) for s, a in
+            (((E, D, F), D), ((E, D, F), D), ((E, F, D), F))]
+
+
+@pytest.mark.parametrize("cls,stores", sorted(WHOLE_LOADS))
+def test_last_rows_of_whole_tiles(cls, stores, experts):
+    import torch
+    import paper_2605_19945_amd as moe
+    rows, heights = WHOLE_LOADS[cls, stores]
+    head, most = sum(rows), 32 * max(heights)
+    ctx = moe.MoEContext(head + most, D, F, E, 1)
+    ctx.moe_set_tile_class(cls)
+    packed = ctx.moe_pack_weights(*[w.cuda() for w in experts])
+    xp = wl.gaussian_bf16_bits(5, cls, (head + most, D), 1.0)
+    off = np.concatenate([[0], np.cumsum(rows + [most])]).astype(np.int32)
+    ref = orc.grouped_ffn(xp, off, *[gu.bits_of(w) for w in experts])
+    x, first = gu.to_dev_bf16(xp), None
+    for n in sorted({32 * h - less for h in heights for less in LAST}):
+        print(f"class {cls}, {stores}, last expert of {n} rows", flush=True)
+        off[E] = head + n
+        y = torch.full((head + n + 32, D), 7.0, dtype=torch.bfloat16, device="cuda")
+        ctx.moe_grouped_ffn(x[:head + n], gu.to_dev(off), head + n, packed, y=y[:head + n])
+        torch.cuda.synchronize()
+        gu.check_output(gu.f64_of_bf16(y[head:head + n]), ref[head:head + n], what=f"class {cls}, {stores}, last {n} rows")
+        assert bool((y[head + n:] == 7.0).all()), f"rows past {n} were written"
+        if first is None:
+            first = y[:head].clone()
+            gu.check_output(gu.f64_of_bf16(first), ref[:head], what=f"class {cls}, {stores}, all rows")
+        assert torch.equal(y[:head], first)
     ctx.close()
