@@ -46,30 +46,36 @@ int gemm_class_rows(int cls) { return kClassRows[cls]; }
 static bool gemm_pick_stream(int cls, double rows_per_expert) { return rows_per_expert <= (double)kClassRows[cls]; }
 
 // Output stores of device scope (bit 0: GEMM1, bit 1: GEMM2).  In the tall class with streamed weights they are up to 9 %
-// faster where a launch is bound by streaming and up to 12 % slower where tiles are short and outputs large.  (Why has
-// not been shown; stores with the non-temporal hint behave much the same.)  From 2280 loads on 253 shapes from d = 256 and
-// f = 256 up -- even, drawn, biased and Zipf-distributed, 26 to 288 rows per expert -- expert GEMMs, us, plain -> device
-// scope in that GEMM:
-//  * GEMM1 gains 1.0 % on average (1.7 up to 180 rows) while the mean load is no more than an eighth of the reduction
-//    length d (a short K loop leaves the stores a larger share of the tile): d = 576, 48 rows 213 -> 203, 240 rows
-//    310 -> 318; d = 1024, 96 rows 182 -> 176, 272 rows 257 -> 261; Mixtral shape, 256 rows 686 -> 676; share of 32
-//    experts, 128 rows 490 -> 476.
-//  * GEMM2 gains 0.7 % there up to 180 rows, and loses as often as it gains elsewhere: the share, 128 rows 490 -> 475; 16
-//    wide experts, 128 rows 738 -> 738; 96 experts, d = 2048, f = 512, 240 rows 181 -> 186.
-// The rule takes 0.7 % off on average (device scope everywhere 0.3 %); 63 of the loads (699) are slower than with
-// plain stores by more than 1 %, 14 (386) by more than 2 %, which is what some loads differ by from run to run with one
-// and the same code.  Of another 720 loads, on another device, 19 (149) and four (71).  The other classes are 0.2 to 0.7 %
-// slower with it (128-row class, 77 tokens, 187.2 against 188.6; decode class 438.3 against 439.2), and launches that
-// share their weight panels gain nothing.
-extern "C" int gemm_pick_scopes(int cls, double rows_per_expert, int d) {
-    if (kClassRows[cls] <= 128 || !gemm_pick_stream(cls, rows_per_expert)) return 0;
-    if (8.0 * rows_per_expert > d) return 0;
-    return rows_per_expert <= 180.0 ? 3 : 1;
+// faster where a launch is bound by streaming from memory, and up to 7 % slower elsewhere.  Why has not been shown: the
+// bytes that pass the L2 are the same with both kinds of store.  Lines, from 3126 loads on 840 shapes (2 to 128 experts, d and
+// f from 256 up, 12 to 288 rows per expert, even, drawn, biased and Zipf-distributed), expert GEMMs, us, plain -> device scope:
+//  * Weights that the 256 MB last-level cache cannot hold from one call to the next.  Below that as many loads are slower by
+//    more than 1 % as faster (16 experts, d = 1728, f = 960, 194 rows 58 -> 60).
+//  * 400 and more work items of GEMM1 with uncut experts.  Up to 256 it gains 0.1 to 0.6 % on average, then 1 to 2 % on uneven loads, and
+//    loses up to 4 % on even ones (16 experts, d = 4032, f = 2304, 176 rows 211 -> 220); from 400 on it gains 2 to 4 % on all kinds
+//    (Mixtral shape, 128 rows 514 -> 475; 16 wide experts, 128 rows 734 -> 697).
+//  * A mean load of no more than an eighth of GEMM1's reduction length d: a short K loop leaves the stores a larger share of
+//    the tile.  It gains 3 % up to there, 1.2 % between a sixth and a quarter with 10 % of the loads slower, and loses beyond.
+//  * GEMM2 as well where its uncut experts fill a round of 256 work items, up to 180 rows: 0.4 to 1.9 % faster, against 0.1 to 0.3 %
+//    slower with fewer items (share of 32 experts, 128 rows 472 -> 452; Mixtral shape: no difference).
+// On the 21 % of the loads that meet this it takes 3.4 % off on average; 0.5 % of them are slower by more than 1 % and none by
+// more than 2, where two copies of one and the same code differ by as much on 1.3 and 0.2 %.  Another 1472 such loads on another
+// device: 3.0 % off, 19 slower by more than 1 % (12 with two copies), six of them again when timed once more (2 to 6 %, all with equal
+// loads of 25 to 30 rows).  With the lines at d / 8 and 180 rows alone, 4 % of the loads were 1 to 4 % slower.  The other
+// classes are 0.2 to 0.7 % slower with device scope (128-row class, 77 tokens, 187.2 against 188.6; decode class 438.3 against
+// 439.2), and launches that share their weight panels gain nothing.
+extern "C" int gemm_pick_scopes(int cls, double rows_per_expert, int E_local, int d, int f) {
+    constexpr double LAST_LEVEL_CACHE = 256.0 * 1024 * 1024;
+    if (kClassRows[cls] <= 128 || !gemm_pick_stream(cls, rows_per_expert) || 8.0 * rows_per_expert > d) return 0;
+    if (6.0 * E_local * d * f < LAST_LEVEL_CACHE) return 0;
+    const int64_t items1 = (int64_t)E_local * ((2 * (int64_t)f + 255) / 256), items2 = (int64_t)E_local * (((int64_t)d + 255) / 256);
+    if (items1 < 400) return 0;
+    return rows_per_expert <= 180.0 && items2 >= 256 ? 3 : 1;
 }
 
-void gemm_pick_hints(GemmPlan* p, double rows_per_expert, int d) {
+void gemm_pick_hints(GemmPlan* p, double rows_per_expert, int E_local, int d, int f) {
     p->w_stream = gemm_pick_stream(p->cls, rows_per_expert);
-    const int scopes = gemm_pick_scopes(p->cls, rows_per_expert, d);
+    const int scopes = gemm_pick_scopes(p->cls, rows_per_expert, E_local, d, f);
     p->scope1 = scopes & 1;
     p->scope2 = scopes & 2;
 }

@@ -147,8 +147,8 @@ GemmPlan gemm_make_plan(int cls, int64_t n_rows_cap, int E_local, int d, int f);
 int gemm_pick_class(double expected_rows_per_expert);
 extern "C" int gemm_pick_class_for(double n_assigned, int E_seen, int E_local, int d, int f);  // (C: called by its test)
 int gemm_class_rows(int cls);
-extern "C" int gemm_pick_scopes(int cls, double rows_per_expert, int d);  // (C: called by its test)
-void gemm_pick_hints(GemmPlan* p, double expected_rows_per_expert, int d);
+extern "C" int gemm_pick_scopes(int cls, double rows_per_expert, int E_local, int d, int f);  // (C: called by its test)
+void gemm_pick_hints(GemmPlan* p, double expected_rows_per_expert, int E_local, int d, int f);
 hipError_t gemm_init_attributes();
 int router_gemm_grid_max(int T_max, int Rp);
 hipError_t launch_router_gemm(const uint16_t* x, const uint16_t* rp, int T, int d, int Rp, float* logits, int ldl,

@@ -36,39 +36,39 @@ def test_rows_at_the_edges_of_the_groups(cls, rows):
     ctx.close()
 
 
-# 128 experts, d = 1024, f = 256: 256 and 512 work items (class 5: 512 and 1024) if no expert is cut, which are whole rounds.
-# Loads by class and kind of stores: rows of all experts but the last, 32-row blocks of the last one.
-E, D, F = 128, 1024, 256
+# 128 experts, d = 1024, f = 256 or 768: 256 or 768 and 512 work items (class 5: 512 and 1024) if no expert is cut, which are
+# whole rounds.  Loads by class and kind of stores: f, rows of all experts but the last, 32-row blocks of the last one.
+E, D = 128, 1024
 TALL = [32 * (5 + e % 5) - (0, 1, 13, 31)[e // 5 % 4] for e in range(E - 1)]
 WHOLE_LOADS = {
-    (1, "plain"): (TALL, (5, 6, 7, 8, 9)),
-    (1, "device scope"): ([n if e % 2 else 1 + e % 32 for e, n in enumerate(TALL)], (5, 6, 7, 8, 9)),
-    (0, "plain"): ([32 * (2 + e % 3) - (0, 5, 31)[e // 3 % 3] for e in range(E - 1)], (2, 3, 4)),
-    (5, "plain"): ([64 - e % 40 for e in range(E - 1)], (1, 2)),
+    (1, "plain"): (256, TALL, (5, 6, 7, 8, 9)),
+    (1, "device scope"): (768, [n if e % 2 else 1 + e % 32 for e, n in enumerate(TALL)], (5, 6, 7, 8, 9)),
+    (0, "plain"): (256, [32 * (2 + e % 3) - (0, 5, 31)[e // 3 % 3] for e in range(E - 1)], (2, 3, 4)),
+    (5, "plain"): (256, [64 - e % 40 for e in range(E - 1)], (1, 2)),
 }
 LAST = (0, 1, 13, 24, 31)  # rows missing from the last block
 
 
-@pytest.fixture(scope="module")
-def experts():
+def experts(f):
     import torch
     g = torch.Generator().manual_seed(3)
     return [torch.empty(s, dtype=torch.bfloat16).normal_(0, a ** -0.5, generator=g) for s, a in
-            (((E, D, F), D), ((E, D, F), D), ((E, F, D), F))]
+            (((E, D, f), D), ((E, D, f), D), ((E, f, D), f))]
 
 
 @pytest.mark.parametrize("cls,stores", sorted(WHOLE_LOADS))
-def test_last_rows_of_whole_tiles(cls, stores, experts):
+def test_last_rows_of_whole_tiles(cls, stores):
     import torch
     import paper_2605_19945_amd as moe
-    rows, heights = WHOLE_LOADS[cls, stores]
+    f, rows, heights = WHOLE_LOADS[cls, stores]
+    weights = experts(f)
     head, most = sum(rows), 32 * max(heights)
-    ctx = moe.MoEContext(head + most, D, F, E, 1)
+    ctx = moe.MoEContext(head + most, D, f, E, 1)
     ctx.moe_set_tile_class(cls)
-    packed = ctx.moe_pack_weights(*[w.cuda() for w in experts])
+    packed = ctx.moe_pack_weights(*[w.cuda() for w in weights])
     xp = wl.gaussian_bf16_bits(5, cls, (head + most, D), 1.0)
     off = np.concatenate([[0], np.cumsum(rows + [most])]).astype(np.int32)
-    ref = orc.grouped_ffn(xp, off, *[gu.bits_of(w) for w in experts])
+    ref = orc.grouped_ffn(xp, off, *[gu.bits_of(w) for w in weights])
     x, first = gu.to_dev_bf16(xp), None
     for n in sorted({32 * h - less for h in heights for less in LAST}):
         print(f"class {cls}, {stores}, last expert of {n} rows", flush=True)

@@ -97,13 +97,13 @@ def test_the_tall_loads_of_the_gpu_tests_keep_their_tiles(lists):
 def test_the_last_expert_of_the_epilogue_tests_keeps_its_tile(lists):
     import ctypes as C
     import paper_2605_19945_amd as moe
-    from test_gpu_epilogue_edges import D, E, F, LAST, WHOLE_LOADS
+    from test_gpu_epilogue_edges import D, E, LAST, WHOLE_LOADS
     pick = moe.load_library().gemm_pick_scopes
-    pick.restype, pick.argtypes = C.c_int, [C.c_int, C.c_double, C.c_int]
-    for (cls, stores), (rows, heights) in WHOLE_LOADS.items():
+    pick.restype, pick.argtypes = C.c_int, [C.c_int, C.c_double, C.c_int, C.c_int, C.c_int]
+    for (cls, stores), (F, rows, heights) in WHOLE_LOADS.items():
         bm, bn = {0: (128, 256), 1: (288, 256), 5: (64, 128)}[cls]
         for n in {32 * h - less for h in heights for less in LAST}:
-            assert pick(cls, (sum(rows) + n) / E, D) == (3 if stores == "device scope" else 0)
+            assert pick(cls, (sum(rows) + n) / E, E, D, F) == (3 if stores == "device scope" else 0)
             for nt in (2 * F // bn, D // bn):
                 _, entries = sched_host.work_list(lists, rows + [n], nt, bm)
                 assert [t[2] for t in entries if t[0] == E - 1] == [n] * nt, (cls, stores, n, nt)
