@@ -223,11 +223,11 @@ static __device__ inline void gemm_epilogue_staged(const f32x4_t (&acc_)[FA][Acc
         }
     }
     // The wavefront reads back only what it wrote itself, GRP wave-level stores at a time: the next group's LDS reads are
-    // under way while this group is stored.  What bounds the way out is that a compute unit takes a 1 KB store in no
-    // less than about 180 cycles, L2 hit or not (64 medium experts, 8192 tokens, GEMM2: without any stores 1119 us
-    // instead of 1256, with all of them into 32 rows for each XCD 1218), so nothing else may stand in line: read, wait and
-    // store one after the other cost a round trip to LDS for each of 36 (layer, us, that -> this: 64 medium experts
-    // 3862 -> 3845, 128 small experts, 8192 tokens, 671 -> 666, Mixtral shape, 4096 tokens, 2111 -> 2104).
+    // under way while this group is stored.  Read, wait and store one after the other cost a round trip to LDS for each of 36
+    // (layer, us, that -> this: 64 medium experts 3862 -> 3845, 128 small experts, 8192 tokens, 671 -> 666, Mixtral shape, 4096
+    // tokens, 2111 -> 2104).  What the stores themselves cost, expert GEMMs without those of GEMM2, us: 64 medium experts, 65536 rows,
+    // 3397 -> 3307, 128 small experts 555 -> 517.  That is 44 and 37 ns for each of the 2048 and 1024 wave-level stores (1 KB) of a
+    // compute unit; with all of them into 32 rows for each XCD (L2 hits) 32 and 26 ns of that go as well.
     const int prow = td.n0 + wn * TN;  // first packed weight row of this wavefront
     if (prow >= Np) return;            // Np is a multiple of 64
     constexpr int RPI = 64 / NCH;      // rows per wave-level store
@@ -559,11 +559,12 @@ static __device__ __forceinline__ void gemm_tile(int bx, const uint16_t* __restr
                     // copy it at the end of a basic block) then sits behind the sub-step's other MFMAs
                     constexpr int g = m / FA;  // place of the token block in the sub-step
                     constexpr int b = FMV <= 8 ? g : (g + 8) % 9;
-                    // the weight blocks there and back, 0 1 2 3 | 3 2 1 0 | ..., so that consecutive MFMAs share an operand,
-                    // also where the token block changes: operands that do not toggle cost no power, and under the
-                    // power limit that is clock (us, 0 1 2 3 throughout -> this: Mixtral shape, 4096 tokens, 2061 -> 2036, 64
-                    // medium experts, 8192 tokens, 3772 -> 3732; the token blocks there and back under a fixed
-                    // weight block: 2076 against 2070 and 3833 against 3828 of this)
+                    // the weight blocks there and back, 0 1 2 3 | 3 2 1 0 | ..., so that consecutive MFMAs share an operand
+                    // within a K half, also where the token block or the token half changes (where the K half or the K step
+                    // changes, both operands do): operands that do not toggle cost no power, and under the power limit
+                    // that is clock (us, 0 1 2 3 throughout -> this: Mixtral shape, 4096 tokens, 2061 -> 2036, 64 medium
+                    // experts, 8192 tokens, 3772 -> 3732; the token blocks there and back under a fixed weight block: 2076
+                    // against 2070 and 3833 against 3828 of this)
                     constexpr int a = ((g + kk * FMV) & 1) ? FA - 1 - m % FA : m % FA;
                     constexpr int t = th * FMV + b;  // 16-row token block
                     if constexpr (b < 8) {
