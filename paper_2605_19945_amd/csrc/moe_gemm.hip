@@ -61,9 +61,10 @@ static bool gemm_pick_stream(int cls, double rows_per_expert) { return rows_per_
 // On the 21 % of the loads that meet this it takes 3.4 % off on average; 0.5 % of them are slower by more than 1 % and none by
 // more than 2, where two copies of one and the same code differ by as much on 1.3 and 0.2 %.  Another 1472 such loads on another
 // device: 3.0 % off, 19 slower by more than 1 % (12 with two copies), six of them again when timed once more (2 to 6 %, all with equal
-// loads of 25 to 30 rows).  With the lines at d / 8 and 180 rows alone, 4 % of the loads were 1 to 4 % slower.  The other
-// classes are 0.2 to 0.7 % slower with device scope (128-row class, 77 tokens, 187.2 against 188.6; decode class 438.3 against
-// 439.2), and launches that share their weight panels gain nothing.
+// loads of 25 to 30 rows); 1272 whole layers: 3.2 % off, none of them twice slower by more than 1 %.  With the lines at d / 8
+// and 180 rows alone, 4 % of the loads were 1 to 4 % slower.  The other classes are 0.2 to 0.7 % slower with device scope
+// (128-row class, 77 tokens, 187.2 against 188.6; decode class 438.3 against 439.2), and launches that share their weight
+// panels gain nothing.
 extern "C" int gemm_pick_scopes(int cls, double rows_per_expert, int E_local, int d, int f) {
     constexpr double LAST_LEVEL_CACHE = 256.0 * 1024 * 1024;
     if (kClassRows[cls] <= 128 || !gemm_pick_stream(cls, rows_per_expert) || 8.0 * rows_per_expert > d) return 0;
